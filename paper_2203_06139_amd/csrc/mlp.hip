@@ -1,13 +1,5 @@
-// mlp.hip -- learned initialiser: rebinning, default starts, and the BF16
-// MFMA training / inference kernels of the 256-512-512-512-5 GELU network.
-//
-// Dense layers use v_mfma_f32_16x16x32_bf16 (gfx950): one wave computes a
-// 32x32 output tile as 2x2 MFMA tiles, each lane feeding 8 consecutive K
-// values of one A row and one B row per instruction, loaded as 16 bytes
-// straight from L2 (the operands of this network are at most a few MB).
-// Every GEMM is "NT": C[m][n] = sum_k A[m][k] B[n][k] with K contiguous in
-// both operands, so the layers also keep transposed copies of activations,
-// adjoints and weights; epilogues fuse bias, GELU, GELU' and BF16 rounding.
+// mlp.hip -- learned initialiser: rebinning, default starts, target maps and
+// column statistics (the network's kernels are in mlp_net.hip).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -15,255 +7,6 @@
 #include "mlp.hpp"
 
 namespace hf {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// FP32 -> BF16 bits, round to nearest even (inputs are finite).
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return static_cast<uint16_t>(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
-
-__device__ __forceinline__ float gelu(float z) { return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f)); }
-__device__ __forceinline__ float gelu_prime(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) +
-         z * 0.39894228040143268f * expf(-0.5f * z * z);
-}
-
-// ---------------------------------------------------------------------------
-// GEMM
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int m0 = blockIdx.y * 64 + (wave >> 1) * 32;
-  const int n0 = blockIdx.x * 64 + (wave & 1) * 32;
-  if (m0 >= g.M || n0 >= g.N) return;  // whole wave; the kernel has no barriers
-  const int r = lane & 15, kq = (lane >> 4) * 8;
-  const uint16_t* a0p = g.A + static_cast<int64_t>(m0 + r) * g.lda + kq;
-  const uint16_t* a1p = a0p + 16 * g.lda;
-  const uint16_t* b0p = g.B + static_cast<int64_t>(n0 + r) * g.ldb + kq;
-  const uint16_t* b1p = b0p + 16 * g.ldb;
-  f32x4 c00 = {0.f, 0.f, 0.f, 0.f}, c01 = c00, c10 = c00, c11 = c00;
-  // kStages K-steps of operands in flight: each step's loads are issued
-  // kStages steps before its MFMAs, so L2 latency overlaps the matrix work
-  // (a plain loop waits for every step's loads in turn).
-  constexpr int kStages = 4;
-  bf16x8 ra0[kStages], ra1[kStages], rb0[kStages], rb1[kStages];
-#pragma unroll
-  for (int s = 0; s < kStages; ++s) {
-    if (s * 32 < g.K) {
-      ra0[s] = *reinterpret_cast<const bf16x8*>(a0p + s * 32);
-      ra1[s] = *reinterpret_cast<const bf16x8*>(a1p + s * 32);
-      rb0[s] = *reinterpret_cast<const bf16x8*>(b0p + s * 32);
-      rb1[s] = *reinterpret_cast<const bf16x8*>(b1p + s * 32);
-    }
-  }
-  for (int k0 = 0; k0 < g.K; k0 += kStages * 32) {
-#pragma unroll
-    for (int s = 0; s < kStages; ++s) {
-      const int k = k0 + s * 32;
-      if (k < g.K) {
-        c00 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra0[s], rb0[s], c00, 0, 0, 0);
-        c01 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra0[s], rb1[s], c01, 0, 0, 0);
-        c10 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra1[s], rb0[s], c10, 0, 0, 0);
-        c11 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ra1[s], rb1[s], c11, 0, 0, 0);
-        const int kn = k + kStages * 32;
-        if (kn < g.K) {
-          ra0[s] = *reinterpret_cast<const bf16x8*>(a0p + kn);
-          ra1[s] = *reinterpret_cast<const bf16x8*>(a1p + kn);
-          rb0[s] = *reinterpret_cast<const bf16x8*>(b0p + kn);
-          rb1[s] = *reinterpret_cast<const bf16x8*>(b1p + kn);
-        }
-      }
-    }
-  }
-  // lane holds D[4 (lane/16) + q][lane % 16] of each 16x16 tile
-  const f32x4 acc[2][2] = {{c00, c01}, {c10, c11}};
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int m = m0 + 16 * i + 4 * (lane >> 4) + q;
-        const int n = n0 + 16 * j + r;
-        float v = acc[i][j][q];
-        if (g.epi == EPI_BIAS_GELU || g.epi == EPI_BIAS) v += g.bias[n];
-        if (g.epi == EPI_BIAS_GELU) {
-          if (g.cf) g.cf[static_cast<int64_t>(m) * g.ldcf + n] = v;  // pre-activation, for GELU'
-          v = gelu(v);
-        } else if (g.epi == EPI_GELU_PRIME) {
-          v *= gelu_prime(g.zin[static_cast<int64_t>(m) * g.ldz + n]);
-        } else {
-          g.cf[static_cast<int64_t>(m) * g.ldcf + n] = v;
-        }
-        if (g.cb) {
-          const uint16_t b = f2bf(v);
-          g.cb[static_cast<int64_t>(m) * g.ldcb + n] = b;
-          if (g.cbt) g.cbt[static_cast<int64_t>(n) * g.ldcbt + m] = b;
-        }
-      }
-}
-
-// Rejects what the kernel cannot index safely: shapes off the 32 grid, row
-// strides that break the 16-byte operand loads, and a missing output or
-// epilogue operand.
-hipError_t gemm_nt(const GemmArgs& g, hipStream_t s) {
-  if (g.M < 32 || g.N < 32 || g.K < 32 || g.M % 32 || g.N % 32 || g.K % 32) return hipErrorInvalidValue;
-  if (!g.A || !g.B || g.lda < g.K || g.ldb < g.K || g.lda % 8 || g.ldb % 8) return hipErrorInvalidValue;
-  const bool bias = g.epi == EPI_BIAS || g.epi == EPI_BIAS_GELU;
-  if (bias && !g.bias) return hipErrorInvalidValue;
-  if ((g.epi == EPI_PLAIN || g.epi == EPI_BIAS) && (!g.cf || g.ldcf < g.N)) return hipErrorInvalidValue;
-  if (g.epi == EPI_BIAS_GELU && g.cf && g.ldcf < g.N) return hipErrorInvalidValue;
-  if (g.epi == EPI_GELU_PRIME && (!g.zin || g.ldz < g.N || !g.cb)) return hipErrorInvalidValue;
-  if (g.epi == EPI_BIAS_GELU && !g.cb) return hipErrorInvalidValue;
-  if ((g.cb && g.ldcb < g.N) || (g.cbt && g.ldcbt < g.M)) return hipErrorInvalidValue;
-  if (g.epi < EPI_PLAIN || g.epi > EPI_GELU_PRIME) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_gemm_nt, dim3((g.N + 63) / 64, (g.M + 63) / 64), dim3(256), 0, s, g);
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Elementwise helpers of the training step
-// ---------------------------------------------------------------------------
-// W fp32 [N][K] -> W bf16 [N][K] and its transpose [K][N].
-__global__ void k_cast_nt(const float* __restrict__ w, int N, int K, uint16_t* __restrict__ wb,
-                          uint16_t* __restrict__ wt) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= static_cast<int64_t>(N) * K) return;
-  const int n = static_cast<int>(i / K), k = static_cast<int>(i % K);
-  const uint16_t b = f2bf(w[i]);
-  wb[i] = b;
-  if (wt) wt[static_cast<int64_t>(k) * N + n] = b;
-}
-
-hipError_t cast_nt(const float* w, int N, int K, uint16_t* wb, uint16_t* wt, hipStream_t s) {
-  const int64_t n = static_cast<int64_t>(N) * K;
-  hipLaunchKernelGGL(k_cast_nt, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, w, N,
-                     K, wb, wt);
-  return hipGetLastError();
-}
-
-// loss = sum_{m, n<5} (y - t)^2 / (5B); dZ = bf16(2 (y - t) / (5B)), zero for
-// the padding columns; written [B][32] and transposed [32][B].  Each block
-// of 256 threads takes 8 rows and writes its FP64 partial sum of squares to
-// part[block]; k_mse_loss then sums the partials in block order.
-__global__ __launch_bounds__(256) void k_mse_grad(const float* __restrict__ y,
-                                                  const float* __restrict__ t, int B,
-                                                  uint16_t* dz, uint16_t* dzt,
-                                                  double* __restrict__ part) {
-  __shared__ double red[256];
-  const int i = blockIdx.x * 256 + threadIdx.x;  // B * 32 is a multiple of 256
-  const int m = i / kMlpOutPad, n = i % kMlpOutPad;
-  const float scale = 2.0f / (5.0f * static_cast<float>(B));
-  float d = 0.0f;
-  double acc = 0.0;
-  if (n < kMlpOut) {
-    d = y[i] - t[m * kMlpOut + n];
-    acc = static_cast<double>(d) * d;
-  }
-  const uint16_t bv = f2bf(scale * d);
-  dz[i] = bv;
-  dzt[static_cast<int64_t>(n) * B + m] = bv;
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ __launch_bounds__(256) void k_mse_loss(const double* __restrict__ part, int nparts, int B,
-                                                  float* loss) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  for (int q = threadIdx.x; q < nparts; q += 256) acc += part[q];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) loss[0] = static_cast<float>(red[0] / (5.0 * B));
-}
-
-hipError_t mse(const float* y, const float* t, int B, float* loss, uint16_t* dz, uint16_t* dzt,
-               double* part, hipStream_t s) {
-  const int nblk = B * kMlpOutPad / 256;
-  hipLaunchKernelGGL(k_mse_grad, dim3(nblk), dim3(256), 0, s, y, t, B, dz, dzt, part);
-  hipLaunchKernelGGL(k_mse_loss, dim3(1), dim3(256), 0, s, part, nblk, B, loss);
-  return hipGetLastError();
-}
-
-// db[n] = sum_m dZ[m][n] (BF16 adjoints, FP32 sums).  A block of 1024
-// threads takes 64 columns: 16 row groups each sum rows g, g+16, ... of one
-// column (coalesced across the 64 lanes), then the 16 group sums are added
-// in group order.
-__global__ __launch_bounds__(1024) void k_bias_grad(const uint16_t* __restrict__ dz, int B, int N,
-                                                    float* __restrict__ db) {
-  __shared__ float red[16][64];
-  const int c = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + c;
-  float acc = 0.0f;
-  if (n < N)
-    for (int m = grp; m < B; m += 16) acc += bf2f(dz[static_cast<int64_t>(m) * N + n]);
-  red[grp][c] = acc;
-  __syncthreads();
-  if (grp == 0 && n < N) {
-    float v = red[0][c];
-#pragma unroll
-    for (int q = 1; q < 16; ++q) v += red[q][c];
-    db[n] = v;
-  }
-}
-
-hipError_t bias_grad(const uint16_t* dz, int B, int N, float* db, hipStream_t s) {
-  hipLaunchKernelGGL(k_bias_grad, dim3((N + 63) / 64), dim3(1024), 0, s, dz, B, N, db);
-  return hipGetLastError();
-}
-
-// AdamW with decoupled weight decay (Loshchilov & Hutter), FP32 state.
-__global__ void k_adamw(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
-                        const float* __restrict__ g, int64_t n, float lr, float wd, float bc1,
-                        float bc2) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = 0.9f * m[i] + 0.1f * gi;
-  const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float mh = mi / bc1, vh = vi / bc2;
-  p[i] -= lr * (mh / (sqrtf(vh) + 1e-8f) + wd * p[i]);
-}
-
-hipError_t adamw(float* p, float* m, float* v, const float* g, int64_t n, float lr, float wd,
-                 int step, hipStream_t s) {
-  const float bc1 = 1.0f - powf(0.9f, static_cast<float>(step));
-  const float bc2 = 1.0f - powf(0.999f, static_cast<float>(step));
-  hipLaunchKernelGGL(k_adamw, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, p, m,
-                     v, g, n, lr, wd, bc1, bc2);
-  return hipGetLastError();
-}
-
-// x fp32 [B][256] -> bf16 [B][256] and transposed [256][B].
-__global__ void k_cast_input(const float* __restrict__ x, int B, uint16_t* a, uint16_t* at) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * kMlpIn) return;
-  const int m = i / kMlpIn, k = i % kMlpIn;
-  const uint16_t b = f2bf(x[i]);
-  a[i] = b;
-  if (at) at[static_cast<int64_t>(k) * B + m] = b;
-}
-
-hipError_t cast_input(const float* x, int B, uint16_t* a, uint16_t* at, hipStream_t s) {
-  hipLaunchKernelGGL(k_cast_input, dim3((B * kMlpIn + 255) / 256), dim3(256), 0, s, x, B, a, at);
-  return hipGetLastError();
-}
 
 // ---------------------------------------------------------------------------
 // Histogram -> network input, default starts, target maps, column statistics
@@ -288,9 +31,9 @@ __device__ __forceinline__ int64_t run_start(int j, int64_t nb) {
 // Rebinning: one block per histogram, S = 2^slog lanes per coarse bin, S the
 // largest power of two not above the run length nb / 256 (at most 16, a DPP
 // row): lane s takes the run's bins s, s + S, ..., so a wave reads segments of
-// up to 64 bytes, and the S partial sums meet in DPP moves.  U coarse bins are summed side by side, which keeps
-// U loads per lane in flight; positions past a run's end are clamped into the
-// histogram and dropped.  Sums of integer-valued counts are exact in FP64 in
+// up to 64 bytes, and the S partial sums meet in DPP moves.  U coarse bins are
+// summed side by side, which keeps U loads per lane in flight; positions past
+// a run's end are clamped into the histogram and dropped.  Sums of integer-valued counts are exact in FP64 in
 // any order; others are added in a fixed order.
 // Bound: HBM, one read of the counts.  4096 histograms of 256..65536 bins
 // (193 MB of u32 counts): 509 us (0.38 TB/s) with one thread walking each
