@@ -59,6 +59,30 @@ __device__ __forceinline__ double exp_fast(double x) {
   return __builtin_amdgcn_ldexp(p, static_cast<int>(k));
 }
 
+// e^x - 1 with the same reduction, x = k ln 2 + r: 2^k (e^r - 1) + (2^k - 1),
+// accurate relative to itself down to x = 0.
+__device__ __forceinline__ double expm1_fast(double x) {
+  x = fmax(x, -746.0);
+  const double k = __builtin_rint(x * kLog2e);
+  double r = fma(-k, kLn2Hi, x);
+  r = fma(-k, kLn2Lo, r);
+  double p = 1.0 / 6227020800.0;     // 1/13!
+  p = fma(p, r, 1.0 / 479001600.0);  // 1/12!
+  p = fma(p, r, 1.0 / 39916800.0);
+  p = fma(p, r, 1.0 / 3628800.0);
+  p = fma(p, r, 1.0 / 362880.0);
+  p = fma(p, r, 1.0 / 40320.0);
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r * r, r);
+  const double s = __builtin_amdgcn_ldexp(1.0, static_cast<int>(k));
+  return fma(s, p, s - 1.0);
+}
+
 // e^x through the FP32 hardware exp2 (about 1e-7 relative for |x| < 8).
 __device__ __forceinline__ double exp_hw32(double x) {
   return static_cast<double>(__builtin_amdgcn_exp2f(static_cast<float>(x * kLog2e)));

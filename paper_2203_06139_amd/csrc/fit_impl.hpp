@@ -27,6 +27,7 @@
 #pragma once
 
 #include <float.h>
+#include <type_traits>
 #include <stdlib.h>
 
 #include "chunk.hpp"
@@ -44,7 +45,7 @@ __device__ __forceinline__ double count_at(const void* base, int dtype, int64_t 
   return static_cast<const double*>(base)[i];
 }
 
-// Entries of the expected Hessian accumulated per pass over the bins.
+// Entries of the expected Hessian summed over the group at a time.
 constexpr int kFisherPass = 32;
 
 template <int NG, int BKG, int BLK>
@@ -58,11 +59,9 @@ struct FitShared {
   double tot[NV];
   double red[BLK / 64][NV];
   double fred[(BLK / 64) * kFisherPass];
-  double ftot[kFisherPass];
   double dmax;
   int redf[BLK / 64];
   int fredf[BLK / 64];
-  int totf, ftotf;
   int chol_ok;
   int fidx[P];
   int nf;
@@ -118,6 +117,57 @@ struct CountsSrc {
   }
 };
 
+// A thread's groups of four counts in the order run_1d takes them: runs of S
+// groups, the threads' runs interleaved.  Counts of u32 type are requested
+// one group ahead, into the registers that the group before has just left, so
+// a group covers the latency of the next; the index is clamped instead of
+// tested, which keeps the loop free of branches.  Where they are read from is
+// a template argument for the same reason.
+enum : int { SRC_LDS = 0, SRC_U32 = 1, SRC_ANY = 2 };
+
+template <int KIND>
+struct RunCounts {
+  const CountsSrc& src;
+  int q, last, skip, S, left;  // group requested; last group; from a run's end to the next run
+  uint4 raw;
+
+  __device__ __forceinline__ RunCounts(const CountsSrc& s, int first, int groups, int per_run,
+                                       int threads)
+      : src(s), q(first * per_run), last(groups - 1), skip((threads - 1) * per_run), S(per_run),
+        left(per_run), raw() {
+    request();
+  }
+  __device__ __forceinline__ void request() {
+    // a histogram starts anywhere in the batch: aligned to its values only
+    typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+    const int g = q < last ? q : last;
+    if constexpr (KIND == SRC_LDS) {
+      raw = reinterpret_cast<const uint4*>(src.lds)[g];
+    } else if constexpr (KIND == SRC_U32) {
+      const u4 v = *reinterpret_cast<const u4*>(static_cast<const uint32_t*>(src.glb) + src.off +
+                                                4 * static_cast<int64_t>(g));
+      raw = uint4{v.x, v.y, v.z, v.w};
+    }
+  }
+  __device__ __forceinline__ void operator()(double (&n)[4]) {
+    if constexpr (KIND == SRC_ANY) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) n[k] = src.at(4 * static_cast<int64_t>(q) + k);
+    } else {
+      n[0] = raw.x;
+      n[1] = raw.y;
+      n[2] = raw.z;
+      n[3] = raw.w;
+    }
+    ++q;
+    if (--left == 0) {
+      left = S;
+      q += skip;
+    }
+    request();
+  }
+};
+
 // The threads that run one fit: the workgroup (BLK = 256 or 512), or one
 // wave (BLK = 64) for the small histograms at the end of the longest-first
 // queue.  gtid is the thread's index in its group, gsync the group's
@@ -139,30 +189,54 @@ __device__ __forceinline__ void gsync() {
   }
 }
 
-template <int NV, int BLK>
-__device__ __forceinline__ void group_sum(double (&v)[NV], int flags, double* tot, int* totf,
-                                          double (*red)[NV], int* redf) {
-  if constexpr (BLK == 64) {
+// Sums v over the group in a fixed order (waves by wave_sum, then the waves in
+// order) and hands thread k < NV the total of component k and the OR of all
+// flags; one barrier before that and one after it.
+template <int NV, int BLK, class Done>
+__device__ __forceinline__ void group_sum(double (&v)[NV], int flags, double (*red)[NV], int* redf,
+                                          Done&& done) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
-    const int f = (__ballot(flags & ST_DOMAIN) ? ST_DOMAIN : 0) |
-                  (__ballot(flags & ST_NONFINITE) ? ST_NONFINITE : 0);
-    if ((threadIdx.x & 63u) == 0) {
+  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
+  const int f = (__ballot(flags & ST_DOMAIN) ? ST_DOMAIN : 0) |
+                (__ballot(flags & ST_NONFINITE) ? ST_NONFINITE : 0);
+  const int wid = BLK == 64 ? 0 : static_cast<int>(threadIdx.x >> 6);
+  if ((threadIdx.x & 63u) == 0) {
 #pragma unroll
-      for (int k = 0; k < NV; ++k) tot[k] = v[k];
-      *totf = f;
-    }
-    gsync<64>();
-  } else {
-    block_sum<NV, BLK / 64>(v, flags, tot, totf, red, redf);
+    for (int k = 0; k < NV; ++k) red[wid][k] = v[k];
+    redf[wid] = f;
   }
+  gsync<BLK>();
+  const int k = gtid<BLK>();
+  if (k < NV) {
+    double x = red[0][k];
+    int o = redf[0];
+#pragma unroll
+    for (int w = 1; w < BLK / 64; ++w) {
+      x += red[w][k];
+      o |= redf[w];
+    }
+    done(k, x, o);
+  }
+  gsync<BLK>();
 }
 
-// Objective (and with GRAD its gradient) of one histogram at sm.th,
-// evaluated by the whole group with the chunked sweep (chunk_1d) in K-bin
-// chunks.  Leaves f in sm.tot[0] (+inf on a domain error) and dL/dtheta_k
-// in sm.tot[1 + k].
-template <int NG, int BKG, int OBJ, bool F32BIN, bool GRAD, int BLK, int K>
+// Totals of an evaluation into sm.tot: f in tot[0] (+inf on a domain error)
+// and dL/dtheta_k in tot[1 + k].
+template <int NG, int BKG, int BLK, int NV>
+__device__ __forceinline__ void publish_totals(FitShared<NG, BKG, BLK>& sm, const Model1D<NG, BKG>& M,
+                                               double (&acc)[NV], int flags) {
+  group_sum<NV, BLK>(acc, flags, reinterpret_cast<double(*)[NV]>(sm.red), sm.redf,
+                     [&](int k, double x, int o) {
+                       if (k == 0 && (o & ST_DOMAIN)) x = __builtin_inf();
+                       sm.tot[k] = k == 0 ? x : x * M.final_factor(k);
+                     });
+}
+
+// Objective (and with GRAD its gradient) of one histogram at sm.th with FP32
+// bins, evaluated by the whole group with the chunked sweep (chunk_1d) in
+// K-bin chunks.  Leaves f in sm.tot[0] (+inf on a domain error) and
+// dL/dtheta_k in sm.tot[1 + k].
+template <int NG, int BKG, int OBJ, bool GRAD, int BLK, int K>
 __device__ __forceinline__ void wg_eval_k(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
     const double2* lut, const CountsSrc& src, int64_t nb, double x0, double hx) {
   constexpr int NV = GRAD ? FitShared<NG, BKG, BLK>::NV : 1;
@@ -184,40 +258,120 @@ __device__ __forceinline__ void wg_eval_k(const FitArgs& a, FitShared<NG, BKG, B
     double l[K];
     const double xs = fma(static_cast<double>(i0), hx, x0);
     if (M.recur)
-      chunk_1d<NG, BKG, OBJ, GRAD, F32BIN, true>(M, lut, xs, n, w, acc, flags, l);
+      chunk_1d<NG, BKG, OBJ, GRAD, true, true>(M, lut, xs, n, w, acc, flags, l);
     else
-      chunk_1d<NG, BKG, OBJ, GRAD, F32BIN, false>(M, lut, xs, n, w, acc, flags, l);
+      chunk_1d<NG, BKG, OBJ, GRAD, true, false>(M, lut, xs, n, w, acc, flags, l);
   }
   for (int64_t i = nch * K + gtid<BLK>(); i < nb; i += BLK) {
     const double n1[1] = {src.at(i)};
     const double w1[1] = {1.0};
     double l1[1];
-    chunk_1d<NG, BKG, OBJ, GRAD, F32BIN, false>(M, lut, fma(static_cast<double>(i), hx, x0), n1, w1,
+    chunk_1d<NG, BKG, OBJ, GRAD, true, false>(M, lut, fma(static_cast<double>(i), hx, x0), n1, w1,
                                                 acc, flags, l1);
   }
-  group_sum<NV, BLK>(acc, flags, sm.tot, &sm.totf, reinterpret_cast<double(*)[NV]>(sm.red),
-                          sm.redf);
-  if (gtid<BLK>() >= 1 && gtid<BLK>() < NV) sm.tot[gtid<BLK>()] *= M.final_factor(gtid<BLK>());
-  if (gtid<BLK>() == 0 && (sm.totf & ST_DOMAIN)) sm.tot[0] = __builtin_inf();
-  gsync<BLK>();
+  publish_totals<NG, BKG, BLK>(sm, M, acc, flags);
 }
 
-template <int NG, int BKG, int OBJ, bool F32BIN, bool GRAD, int BLK>
-__device__ __forceinline__ void wg_eval(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
-    const double2* lut, const CountsSrc& src, int64_t nb, double x0, double hx) {
-  if constexpr (fit_chunk_large<NG, BKG, BLK>()) {
-    if (nb >= static_cast<int64_t>(kFitChunkLarge) * BLK) {
-      wg_eval_k<NG, BKG, OBJ, F32BIN, GRAD, BLK, kFitChunkLarge>(a, sm, lut, src, nb, x0, hx);
-      return;
+// Groups of four bins per run of the FP64 sweep: the S <= kRunGroups with
+// the least work on the busiest thread, counting a run's start and expansion
+// (two exps per Gaussian and the moments) as kRunStart bins.
+constexpr int kRunGroups = 8;
+
+// Groups of four bins that are taken in runs; the bins after them are taken
+// one by one (at most three, and those beyond 2^31).
+__device__ __forceinline__ int run_quads(int64_t nb) {
+  return nb < (int64_t(1) << 31) ? static_cast<int>(nb / 4) : (1 << 29) - (1 << 16);
+}
+
+template <int NG>
+__device__ __forceinline__ int run_groups(int64_t nb, int threads) {
+  constexpr unsigned kRunStart = 2 + NG;
+  const unsigned n = run_quads(nb);
+  int best = 1;
+  unsigned cost = ~0u;
+#pragma unroll
+  for (int S = 1; S <= kRunGroups; ++S) {
+    const unsigned runs = (n + S - 1) / S;
+    const unsigned c = (runs + threads - 1) / threads * (4 * S + kRunStart);
+    if (c < cost) {
+      cost = c;
+      best = S;
     }
   }
-  wg_eval_k<NG, BKG, OBJ, F32BIN, GRAD, BLK, kFitChunkSmall>(a, sm, lut, src, nb, x0, hx);
+  return best;
 }
 
-// mu(x) and dmu/dtheta by their closed forms, one exp per Gaussian (the
-// Fisher pass runs once per fit, so it does without the recurrence):
-//   dG/dA = e, dG/dm = G z / s, dG/ds = G z^2 / s with z = (x - m)/s;
-//   polynomial t^j; exponential E and t E.
+// The same evaluation in FP64 by runs of S groups of four bins (run_1d), in
+// single groups where a run is too long for the recurrences, and bin by bin
+// where four bins are.  Bound: VALU issue, about 43 instructions per bin.
+// Against four-bin chunks, each with its own exps and expansion, and counts
+// read as they were needed: one evaluation and iteration of a 65,536-bin
+// Gauss + exponential histogram on 256 threads 67.5 -> 32 us; 4096 such
+// histograms of 256..65536 bins 1.84 -> 1.14 ms; 512 of three Gaussians + line
+// on 10,000 bins 0.70 -> 0.33 ms (280 -> 256 registers: two waves per SIMD).
+template <int NG, int BKG, int OBJ, bool GRAD, int BLK>
+__device__ __forceinline__ void wg_eval_runs(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
+    const double2* lut, const CountsSrc& src, int64_t nb, double x0, double hx, int S) {
+  constexpr int NV = GRAD ? FitShared<NG, BKG, BLK>::NV : 1;
+  const int tid = gtid<BLK>();
+  Model1D<NG, BKG> M;
+  M.init(sm.th, a.t_shift, a.t_scale);
+  M.init_grid(hx, 4 * S);
+  if (!M.recur && S > 1) {
+    S = 1;
+    M.recur = M.recurs(4);
+  }
+  double acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+  int flags = 0;
+  const int nq = run_quads(nb);
+  if (M.recur && nq > 0) {
+    auto runs = [&](auto kind) {
+      RunCounts<decltype(kind)::value> next(src, tid, nq, S, BLK);
+      for (int q = tid * S; q < nq; q += BLK * S)
+        run_1d<NG, BKG, OBJ, GRAD>(M, lut, fma(4.0 * q, hx, x0), nq - q < S ? nq - q : S, next, acc,
+                                   flags);
+    };
+    if (src.lds)
+      runs(std::integral_constant<int, SRC_LDS>{});
+    else if (src.dtype == DT_U32)
+      runs(std::integral_constant<int, SRC_U32>{});
+    else
+      runs(std::integral_constant<int, SRC_ANY>{});
+  }
+  const double w1[1] = {1.0};
+  for (int64_t i = (M.recur ? 4 * static_cast<int64_t>(nq) : 0) + tid; i < nb; i += BLK) {
+    const double n1[1] = {src.at(i)};
+    double l1[1];
+    chunk_1d<NG, BKG, OBJ, GRAD, false, false>(M, lut, fma(static_cast<double>(i), hx, x0), n1, w1,
+                                               acc, flags, l1);
+  }
+  publish_totals<NG, BKG, BLK>(sm, M, acc, flags);
+}
+
+// S: run_groups() of the histogram.  FP32 bins take their exps per chunk in
+// FP32, which is part of their results, and keep the chunked sweep.
+template <int NG, int BKG, int OBJ, bool F32BIN, bool GRAD, int BLK>
+__device__ __forceinline__ void wg_eval(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
+    const double2* lut, const CountsSrc& src, int64_t nb, double x0, double hx, int S) {
+  if constexpr (!F32BIN) {
+    wg_eval_runs<NG, BKG, OBJ, GRAD, BLK>(a, sm, lut, src, nb, x0, hx, S);
+  } else {
+    if constexpr (fit_chunk_large<NG, BKG, BLK>()) {
+      if (nb >= static_cast<int64_t>(kFitChunkLarge) * BLK) {
+        wg_eval_k<NG, BKG, OBJ, GRAD, BLK, kFitChunkLarge>(a, sm, lut, src, nb, x0, hx);
+        return;
+      }
+    }
+    wg_eval_k<NG, BKG, OBJ, GRAD, BLK, kFitChunkSmall>(a, sm, lut, src, nb, x0, hx);
+  }
+}
+
+// mu(x) and dmu/dtheta by their closed forms, one exp per Gaussian, for bins
+// outside the runs:
+//   dG/dA = e, dG/dm = G z / s, dG/ds = G z^2 / s with z = (x - m)/s, the
+//   1/s left to Model1D::final_factor; polynomial t^j; exponential E and t E.
 template <int NG, int BKG>
 __device__ __forceinline__ double mu_partials(const Model1D<NG, BKG>& M, double x,
                                               double (&v)[Shape1D<NG, BKG>::P]) {
@@ -230,8 +384,8 @@ __device__ __forceinline__ double mu_partials(const Model1D<NG, BKG>& M, double 
     const double G = M.A[g] * e;
     mu += G;
     v[3 * g] = e;
-    v[3 * g + 1] = G * z * M.is[g];
-    v[3 * g + 2] = G * z * z * M.is[g];
+    v[3 * g + 1] = G * z;
+    v[3 * g + 2] = G * z * z;
   }
   const double t = (x - M.tshift) * M.ta;
   if constexpr (BKG == BKG_EXP) {
@@ -251,46 +405,134 @@ __device__ __forceinline__ double mu_partials(const Model1D<NG, BKG>& M, double 
   return mu;
 }
 
+// Weight c of the expected Hessian, 0 where the bin is skipped.
+template <int OBJ>
+__device__ __forceinline__ double fisher_weight(double n, double mu) {
+  if constexpr (OBJ == OBJ_NEYMAN) return n > 0.0 ? 2.0 * rcp_fast(n) : 0.0;
+  const double c = mu > 0.0 ? rcp_fast(fmax(mu, 1e-300)) : 0.0;
+  return OBJ == OBJ_PEARSON ? 2.0 * c : c;
+}
+
+// acc[q] += c v_a v_b for the upper-triangle entries E0 .. E0 + NQ.
+template <int P, int E0, int NQ>
+__device__ __forceinline__ void fisher_add(double c, const double (&v)[P], double (&acc)[NQ]) {
+  constexpr TriIndex<P> tri{};
+  if (c > 0.0 && __builtin_isfinite(c)) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q] = fma(c * v[tri.a[E0 + q]], v[tri.b[E0 + q]], acc[q]);
+  }
+}
+
+// The partials of a run of bins by the recurrences of run_1d, without the 1/s
+// of the mean and width columns (Model1D::final_factor).
+template <int NG, int BKG, int OBJ, int E0, int NQ, class Next>
+__device__ __forceinline__ void fisher_run(const Model1D<NG, BKG>& M, double xs, int quads, Next&& next,
+                                           double (&acc)[NQ]) {
+  using S = Shape1D<NG, BKG>;
+  constexpr int G1 = NG > 0 ? NG : 1;
+  double z[G1], e[G1], r[G1];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    z[g] = (xs - M.m[g]) * M.is[g];
+    e[g] = exp_fast(-0.5 * z[g] * z[g]);
+    r[g] = exp_fast(clamp_ratio_exponent<false>(fma(-M.dz[g], z[g], -0.5 * M.dz[g] * M.dz[g])));
+  }
+  double t = (xs - M.tshift) * M.ta;
+  double E = 0.0;
+  if constexpr (BKG == BKG_EXP) E = exp_fast(fma(M.c[1], t, M.c[0]));
+#pragma unroll 1
+  for (int q = 0; q < quads; ++q) {
+    double n[4] = {};
+    if constexpr (OBJ == OBJ_NEYMAN) next(n);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      double v[S::P], mu = 0.0;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const double G = M.A[g] * e[g];
+        mu += G;
+        v[3 * g] = e[g];
+        v[3 * g + 1] = G * z[g];
+        v[3 * g + 2] = v[3 * g + 1] * z[g];
+        e[g] *= r[g];
+        r[g] *= M.D[g];
+        z[g] += M.dz[g];
+      }
+      if constexpr (BKG == BKG_EXP) {
+        mu += E;
+        v[3 * NG] = E;
+        v[3 * NG + 1] = t * E;
+        E *= M.qE;
+      } else if constexpr (S::NB > 0) {
+        double tj = 1.0;
+#pragma unroll
+        for (int j = 0; j < S::NB; ++j) {
+          mu = fma(M.c[j], tj, mu);
+          v[3 * NG + j] = tj;
+          tj *= t;
+        }
+      }
+      t += M.dt;
+      fisher_add<S::P, E0>(fisher_weight<OBJ>(n[k], mu), v, acc);
+    }
+  }
+}
+
 // Expected Hessian at theta0, F = sum_i c_i (dmu_i/dtheta)(dmu_i/dtheta)^T
 // with c_i = d^2 l/d mu^2 at n_i = mu_i (1/mu Poisson, 2/mu Pearson, 2/n for
 // n > 0 Neyman); bins whose c_i is not finite and positive are skipped.  The
-// upper triangle is accumulated kFisherPass entries per pass over the bins
-// and written symmetrically into sm.H.
+// upper triangle is accumulated up to kFisherWide entries per pass over the
+// bins (one pass for P <= 11, two up to 16), summed over the group
+// kFisherPass entries at a time and written symmetrically into sm.H.
+constexpr int kFisherWide = 72;
 template <int NG, int BKG, int OBJ, int PASS, int BLK>
 __device__ __forceinline__ void fisher_pass(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
-    const CountsSrc& src, int64_t nb, double x0, double hx) {
+    const CountsSrc& src, int64_t nb, double x0, double hx, int S) {
   constexpr int P = FitShared<NG, BKG, BLK>::P;
   constexpr TriIndex<P> tri{};
-  constexpr int E0 = PASS * kFisherPass;
-  if constexpr (E0 < TriIndex<P>::N) {
-    constexpr int NQ = (TriIndex<P>::N - E0 < kFisherPass) ? TriIndex<P>::N - E0 : kFisherPass;
+  constexpr int N = TriIndex<P>::N;
+  constexpr int W = (N + (N + kFisherWide - 1) / kFisherWide - 1) / ((N + kFisherWide - 1) / kFisherWide);
+  constexpr int E0 = PASS * W;
+  if constexpr (E0 < N) {
+    constexpr int NQ = (N - E0 < W) ? N - E0 : W;
+    const int tid = gtid<BLK>();
     Model1D<NG, BKG> M;
     M.init(sm.th0, a.t_shift, a.t_scale);
+    M.init_grid(hx, 4 * S);
+    if (!M.recur && S > 1) {
+      S = 1;
+      M.recur = M.recurs(4);
+    }
     double acc[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) acc[q] = 0.0;
-    for (int64_t i = gtid<BLK>(); i < nb; i += BLK) {
+    const int nq = run_quads(nb);
+    if (M.recur && nq > 0) {
+      RunCounts<SRC_ANY> next(src, tid, nq, S, BLK);  // only Neyman's weight reads the counts
+      for (int q = tid * S; q < nq; q += BLK * S)
+        fisher_run<NG, BKG, OBJ, E0>(M, fma(4.0 * q, hx, x0), nq - q < S ? nq - q : S, next, acc);
+    }
+    for (int64_t i = (M.recur ? 4 * static_cast<int64_t>(nq) : 0) + tid; i < nb; i += BLK) {
       double v[P];
       const double mu = mu_partials(M, fma(static_cast<double>(i), hx, x0), v);
-      double c;
-      if constexpr (OBJ == OBJ_POISSON) c = 1.0 / mu;
-      else if constexpr (OBJ == OBJ_PEARSON) c = 2.0 / mu;
-      else {
-        const double n = src.at(i);
-        c = n > 0.0 ? 2.0 / n : 0.0;
-      }
-      if (c > 0.0 && __builtin_isfinite(c)) {
+      fisher_add<P, E0>(fisher_weight<OBJ>(OBJ == OBJ_NEYMAN ? src.at(i) : 0.0, mu), v, acc);
+    }
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) acc[q] = fma(c * v[tri.a[E0 + q]], v[tri.b[E0 + q]], acc[q]);
-      }
+    for (int c0 = 0; c0 < NQ; c0 += kFisherPass) {
+      double part[kFisherPass];
+#pragma unroll
+      for (int q = 0; q < kFisherPass; ++q) part[q] = c0 + q < NQ ? acc[c0 + q < NQ ? c0 + q : 0] : 0.0;
+      group_sum<kFisherPass, BLK>(
+          part, 0, reinterpret_cast<double(*)[kFisherPass]>(sm.fred), sm.fredf,
+          [&](int k, double x, int) {
+            if (c0 + k >= NQ) return;
+            const int r = tri.a[E0 + c0 + k], c = tri.b[E0 + c0 + k];
+            const double f = x * M.final_factor(1 + r) * M.final_factor(1 + c);
+            sm.H[r * P + c] = f;
+            sm.H[c * P + r] = f;
+          });
     }
-    group_sum<NQ, BLK>(acc, 0, sm.ftot, &sm.ftotf, reinterpret_cast<double(*)[NQ]>(sm.fred), sm.fredf);
-    if (gtid<BLK>() < NQ) {
-      const int r = tri.a[E0 + gtid<BLK>()], c = tri.b[E0 + gtid<BLK>()];
-      sm.H[r * P + c] = sm.ftot[gtid<BLK>()];
-      sm.H[c * P + r] = sm.ftot[gtid<BLK>()];
-    }
-    fisher_pass<NG, BKG, OBJ, PASS + 1, BLK>(a, sm, src, nb, x0, hx);
+    fisher_pass<NG, BKG, OBJ, PASS + 1, BLK>(a, sm, src, nb, x0, hx, S);
   }
 }
 
@@ -379,75 +621,13 @@ __device__ __forceinline__ double dot_lds(const double* x, const double* y, int 
   return s;
 }
 
-// f(u) and g_u = sigma * dL/dtheta at theta = theta0 + sigma * u.
-template <int NG, int BKG, int OBJ, int BLK>
-__device__ __forceinline__ double wg_objective(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
-    const double2* lut, const CountsSrc& src, const double* uu, double* gout, bool f32, int64_t nb,
-    double x0, double hx) {
-  constexpr int P = FitShared<NG, BKG, BLK>::P;
-  const int tid = gtid<BLK>();
-  if (tid < P) sm.th[tid] = sm.th0[tid];
-  gsync<BLK>();
-  if (tid < sm.nf) {
-    const int k = sm.fidx[tid];
-    sm.th[k] = fma(sm.sig[k], uu[tid], sm.th0[k]);
-  }
-  gsync<BLK>();
-  if (f32)
-    wg_eval<NG, BKG, OBJ, true, true, BLK>(a, sm, lut, src, nb, x0, hx);
-  else
-    wg_eval<NG, BKG, OBJ, false, true, BLK>(a, sm, lut, src, nb, x0, hx);
-  if (tid < sm.nf) {
-    const int k = sm.fidx[tid];
-    gout[tid] = sm.sig[k] * sm.tot[1 + k];
-  }
-  const double f = sm.tot[0];
-  gsync<BLK>();
-  return f;
-}
-
-// f(u) alone (FP64 bins): the value the finite-difference gradient and its
-// line search need.
-template <int NG, int BKG, int OBJ, int BLK>
-__device__ __forceinline__ double wg_value(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
-    const double2* lut, const CountsSrc& src, const double* uu, int64_t nb, double x0, double hx) {
-  constexpr int P = FitShared<NG, BKG, BLK>::P;
-  const int tid = gtid<BLK>();
-  if (tid < P) sm.th[tid] = sm.th0[tid];
-  gsync<BLK>();
-  if (tid < sm.nf) {
-    const int k = sm.fidx[tid];
-    sm.th[k] = fma(sm.sig[k], uu[tid], sm.th0[k]);
-  }
-  gsync<BLK>();
-  wg_eval<NG, BKG, OBJ, false, false, BLK>(a, sm, lut, src, nb, x0, hx);
-  const double f = sm.tot[0];
-  gsync<BLK>();
-  return f;
-}
-
 // Central differences in the scaled coordinates, the gradient a fitter
 // without derivatives of the model uses: g_q = (f(u + h e_q) - f(u - h e_q))
 // / (2h) with h = kFdStep max(1, |u_q|), 2 nf objective sweeps.
 constexpr double kFdStep = 1e-4;
 
-template <int NG, int BKG, int OBJ, int BLK>
-__device__ __forceinline__ void wg_fd_grad(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
-    const double2* lut, const CountsSrc& src, const double* uu, double* gout, int64_t nb, double x0,
-    double hx) {
-  const int tid = gtid<BLK>();
-  const int nf = sm.nf;
-  for (int q = 0; q < nf; ++q) {
-    const double h = kFdStep * fmax(1.0, fabs(uu[q]));
-    const double up = uu[q] + h, um = uu[q] - h;
-    if (tid < nf) sm.up[tid] = (tid == q) ? up : uu[tid];
-    const double fp = wg_value<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.up, nb, x0, hx);
-    if (tid < nf) sm.up[tid] = (tid == q) ? um : uu[tid];
-    const double fm = wg_value<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.up, nb, x0, hx);
-    if (tid == 0) gout[q] = (fp - fm) / (up - um);
-  }
-  gsync<BLK>();
-}
+// What an evaluation was for (see fit_one).
+enum : int { EV_INIT = 0, EV_POLISH, EV_SEARCH, EV_FINAL, EV_FD_PLUS, EV_FD_MINUS };
 
 template <int NG, int BKG, int OBJ, int BLK>
 __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
@@ -471,6 +651,7 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
   }
   const double hx = (hi - lo) / static_cast<double>(nb);
   const double x0 = lo + 0.5 * hx;
+  const int S = run_groups<NG>(nb, BLK);
   CountsSrc src{nullptr, a.counts, a.dtype, off};
   if (a.dtype == DT_U32 && nb <= cache_cap) {  // keep the counts in LDS for all evaluations
     const uint32_t* g = static_cast<const uint32_t*>(a.counts) + off;
@@ -478,7 +659,7 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
     src.lds = cache;
   }
 
-  if (tid < P) sm.th0[tid] = a.theta0[static_cast<int64_t>(b) * P + tid];
+  if (tid < P) sm.th0[tid] = sm.th[tid] = a.theta0[static_cast<int64_t>(b) * P + tid];
   gsync<BLK>();
   if (tid == 0) {
     const double rx = hi - lo;
@@ -494,96 +675,107 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
       if (a.free_mask == 0u || ((a.free_mask >> q) & 1u)) sm.fidx[nf++] = q;
     sm.nf = nf;
   }
-  if (tid < P) sm.u[tid] = 0.0;
+  if (tid < P) sm.u[tid] = sm.un[tid] = 0.0;
   for (int t = tid; t < P * P; t += BLK) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
   gsync<BLK>();
   const int nf = sm.nf;
   bool first = true;
   if (a.hessian_init == 1 && nf > 0) {
-    fisher_pass<NG, BKG, OBJ, 0, BLK>(a, sm, src, nb, x0, hx);
+    fisher_pass<NG, BKG, OBJ, 0, BLK>(a, sm, src, nb, x0, hx, S);
     first = !fisher_start(sm, nf);  // no first-update scaling after a Fisher start
   }
 
   bool f32 = a.f32 != 0;
   const bool fd = a.fd_grad != 0;  // central differences (FP64 bins only)
-  double f;
-  int nev = 1, it = 0, status = FIT_MAXITER;
-  if (fd) {
-    f = wg_value<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.u, nb, x0, hx);
-    if (__builtin_isfinite(f)) {
-      wg_fd_grad<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.u, sm.g, nb, x0, hx);
-      nev += 2 * nf;
-    }
-  } else {
-    f = wg_objective<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.u, sm.g, f32, nb, x0, hx);
-  }
-  if (!__builtin_isfinite(f)) {
-    status = (f == __builtin_inf()) ? FIT_DOMAIN : FIT_NONFINITE;
-  } else {
-    while (it < a.max_iter) {
-      if (tid < nf) {
-        double hg = 0.0;
-        hg = dot_lds<P>(&sm.H[tid * P], sm.g, nf);
-        sm.pv[tid] = -hg;
-        sm.tmp[tid] = sm.g[tid] * hg;
-      }
-      gsync<BLK>();
-      double edm = 0.0;
-      edm = dot_lds<P>(sm.tmp, nullptr, nf);
-      edm *= 0.5;
-      const double goal = fmax(a.edm_tol, 4.0 * DBL_EPSILON * fabs(f));
-      if (f32 && a.polish_edm > 0.0 && edm < a.polish_edm) {
-        // switch to FP64 bins for the rest of the fit
-        f32 = false;
-        f = wg_objective<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.u, sm.g, false, nb, x0, hx);
-        ++nev;
-        if (!__builtin_isfinite(f)) {
-          status = (f == __builtin_inf()) ? FIT_DOMAIN : FIT_NONFINITE;
-          break;
-        }
+  const int kq = tid < nf ? sm.fidx[tid] : 0;           // this thread's free parameter
+  const double sq = tid < nf ? sm.sig[kq] : 0.0;        // and its scale
+  double f = 0.0, fn = 0.0, nll = 0.0, edm = 0.0, goal = 0.0, slope = 0.0, alpha = 1.0;
+  double fp = 0.0, hp = 0.0, hm = 0.0;  // central differences: value and points of one side
+  int nev = 1, it = 0, ls = 0, q = 0, status = FIT_MAXITER;
+  int stage = EV_INIT, after = EV_INIT;
+  // Every evaluation of a fit passes through this one place, at the point
+  // sm.un (sm.up for central differences), and `stage` says what it was for:
+  // the compiler then builds each sweep once per thread group.
+  for (;;) {
+    if (tid < nf) sm.th[kq] = fma(sq, stage >= EV_FD_PLUS ? sm.up[tid] : sm.un[tid], sm.th0[kq]);
+    gsync<BLK>();
+    if (fd)
+      wg_eval<NG, BKG, OBJ, false, false, BLK>(a, sm, lut, src, nb, x0, hx, S);
+    else if (f32 && stage != EV_FINAL)
+      wg_eval<NG, BKG, OBJ, true, true, BLK>(a, sm, lut, src, nb, x0, hx, S);
+    else
+      wg_eval<NG, BKG, OBJ, false, true, BLK>(a, sm, lut, src, nb, x0, hx, S);
+    const double fe = sm.tot[0];
+    bool accepted = false;
+    if (stage == EV_FINAL) {
+      nll = fe;
+      break;
+    } else if (stage == EV_FD_PLUS) {
+      fp = fe;
+      if (tid < nf) sm.up[tid] = tid == q ? hm : sm.un[tid];
+      stage = EV_FD_MINUS;
+      continue;
+    } else if (stage == EV_FD_MINUS) {
+      if (tid == 0) sm.gn[q] = (fp - fe) / (hp - hm);
+      if (++q < nf) {
+        const double h = kFdStep * fmax(1.0, fabs(sm.un[q]));
+        hp = sm.un[q] + h;
+        hm = sm.un[q] - h;
+        if (tid < nf) sm.up[tid] = tid == q ? hp : sm.un[tid];
+        stage = EV_FD_PLUS;
         continue;
       }
-      if (!a.fixed_iters && edm < goal) {
-        status = FIT_CONVERGED;
-        break;
-      }
-      double slope = 0.0;
-      slope = dot_lds<P>(sm.g, sm.pv, nf);
-      if (!(slope < 0.0)) {  // H lost positive definiteness: restart from I
-        gsync<BLK>();
-        for (int t = tid; t < P * P; t += BLK) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
-        if (tid < nf) sm.pv[tid] = -sm.g[tid];
-        first = true;
-        gsync<BLK>();
-        slope = 0.0;
-        slope = -dot_lds<P>(sm.g, sm.g, nf);
-      }
-      double alpha = 1.0, fn = 0.0;
-      bool accepted = false;
-      for (int ls = 0; ls < a.ls_max; ++ls) {
-        if (tid < nf) sm.un[tid] = sm.u[tid] + alpha * sm.pv[tid];
-        gsync<BLK>();
-        fn = fd ? wg_value<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.un, nb, x0, hx)
-                : wg_objective<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.un, sm.gn, f32, nb, x0, hx);
+      nev += 2 * nf;
+      gsync<BLK>();
+      accepted = after == EV_SEARCH;
+    } else {
+      fn = fe;
+      if (stage == EV_SEARCH) {
         ++nev;
-        if (__builtin_isfinite(fn) && fn <= f + 1e-4 * alpha * slope) {
+        if (!(__builtin_isfinite(fn) && fn <= f + 1e-4 * alpha * slope)) {
+          alpha *= 0.5;
+          if (++ls < a.ls_max) {
+            if (tid < nf) sm.un[tid] = sm.u[tid] + alpha * sm.pv[tid];
+            continue;
+          }
+          status = (edm < goal) ? FIT_CONVERGED : FIT_LSFAIL;
+        } else {
           accepted = true;
-          break;
+          ++it;
         }
-        alpha *= 0.5;
+      } else {
+        f = fn;
+        if (!__builtin_isfinite(f))
+          status = (f == __builtin_inf()) ? FIT_DOMAIN : FIT_NONFINITE;
       }
-      if (!accepted) {
-        status = (edm < goal) ? FIT_CONVERGED : FIT_LSFAIL;
+      const bool go_on = stage == EV_SEARCH ? accepted : __builtin_isfinite(f);
+      if (!go_on) {
+        if (f32 && __builtin_isfinite(f)) {
+          stage = EV_FINAL;
+          if (tid < nf) sm.un[tid] = sm.u[tid];
+          continue;
+        }
+        nll = f;
         break;
       }
-      ++it;
-      if (fd) {  // the gradient only at the accepted point
-        wg_fd_grad<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.un, sm.gn, nb, x0, hx);
-        nev += 2 * nf;
+      if (fd && nf > 0) {  // the gradient, only at accepted points
+        after = stage;
+        q = 0;
+        const double h = kFdStep * fmax(1.0, fabs(sm.un[0]));
+        hp = sm.un[0] + h;
+        hm = sm.un[0] - h;
+        if (tid < nf) sm.up[tid] = tid == 0 ? hp : sm.un[tid];
+        stage = EV_FD_PLUS;
+        continue;
       }
+    }
+    // gradient at the new point, in the scaled coordinates
+    double gq = 0.0;
+    if (tid < nf) gq = fd ? sm.gn[tid] : sq * sm.tot[1 + kq];
+    if (accepted) {
       if (tid < nf) {
         sm.sv[tid] = sm.un[tid] - sm.u[tid];
-        sm.yv[tid] = sm.gn[tid] - sm.g[tid];
+        sm.yv[tid] = gq - sm.g[tid];
       }
       gsync<BLK>();
       const double sy = dot_lds<P>(sm.sv, sm.yv, nf);
@@ -596,14 +788,9 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
           first = false;
           gsync<BLK>();
         }
-        if (tid < nf) {
-          double hy = 0.0;
-          hy = dot_lds<P>(&sm.H[tid * P], sm.yv, nf);
-          sm.Hy[tid] = hy;
-        }
+        if (tid < nf) sm.Hy[tid] = dot_lds<P>(&sm.H[tid * P], sm.yv, nf);
         gsync<BLK>();
-        double yHy = 0.0;
-        yHy = dot_lds<P>(sm.yv, sm.Hy, nf);
+        const double yHy = dot_lds<P>(sm.yv, sm.Hy, nf);
         const double rho = 1.0 / sy;
         const double cc = rho * rho * yHy + rho;
         for (int t = tid; t < nf * nf; t += BLK) {
@@ -611,16 +798,55 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
           sm.H[r * P + c] += -rho * (sm.Hy[r] * sm.sv[c] + sm.sv[r] * sm.Hy[c]) + cc * sm.sv[r] * sm.sv[c];
         }
       }
-      if (tid < nf) {
-        sm.u[tid] = sm.un[tid];
-        sm.g[tid] = sm.gn[tid];
-      }
-      gsync<BLK>();
       f = fn;
     }
+    if (tid < nf) {
+      sm.u[tid] = sm.un[tid];
+      sm.g[tid] = gq;
+    }
+    gsync<BLK>();
+    // direction p = -H g
+    stage = EV_SEARCH;
+    if (it < a.max_iter) {
+      if (tid < nf) {
+        const double hg = dot_lds<P>(&sm.H[tid * P], sm.g, nf);
+        sm.pv[tid] = -hg;
+        sm.tmp[tid] = sm.g[tid] * hg;
+      }
+      gsync<BLK>();
+      edm = 0.5 * dot_lds<P>(sm.tmp, nullptr, nf);
+      goal = fmax(a.edm_tol, 4.0 * DBL_EPSILON * fabs(f));
+      if (f32 && a.polish_edm > 0.0 && edm < a.polish_edm) {
+        // switch to FP64 bins for the rest of the fit
+        f32 = false;
+        ++nev;
+        stage = EV_POLISH;  // at sm.un = sm.u
+        continue;
+      }
+      if (!a.fixed_iters && edm < goal) {
+        status = FIT_CONVERGED;
+      } else {
+        slope = dot_lds<P>(sm.g, sm.pv, nf);
+        if (!(slope < 0.0)) {  // H lost positive definiteness: restart from I
+          gsync<BLK>();
+          for (int t = tid; t < P * P; t += BLK) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
+          if (tid < nf) sm.pv[tid] = -sm.g[tid];
+          first = true;
+          gsync<BLK>();
+          slope = -dot_lds<P>(sm.g, sm.g, nf);
+        }
+        alpha = 1.0;
+        ls = 0;
+        if (tid < nf) sm.un[tid] = sm.u[tid] + alpha * sm.pv[tid];
+        continue;
+      }
+    }
+    if (!f32) {  // else the NLL at sm.un = sm.u once more with FP64 bins
+      nll = f;
+      break;
+    }
+    stage = EV_FINAL;
   }
-  double nll = f;
-  if (f32 && __builtin_isfinite(f)) nll = wg_objective<NG, BKG, OBJ, BLK>(a, sm, lut, src, sm.u, sm.gn, false, nb, x0, hx);
   // final parameters, canonicalised
   if (tid < P) sm.th[tid] = sm.th0[tid];
   gsync<BLK>();
@@ -658,7 +884,7 @@ constexpr size_t wave_slot_bytes(int wave_bins) {
 }
 
 template <int NG, int BKG, int OBJ, int BLK>
-__global__ __launch_bounds__(BLK) void k_fit(FitArgs a) {
+__global__ __launch_bounds__(BLK, 2) void k_fit(FitArgs a) {
   __shared__ FitShared<NG, BKG, BLK> sm;
   __shared__ double2 lut[OBJ == OBJ_POISSON ? kLogLut : 1];
   // the workgroup's count cache, or the waves' slots
