@@ -936,7 +936,7 @@ HF_EXPORT int hf_fit_set_wave_bins(hf_ctx* c, int32_t wave_bins) {
 }
 
 HF_EXPORT int hf_fit_get_wave_bins(const hf_ctx* c) {
-  return c ? c->fit.wave_bins : HF_EINVAL;
+  return c ? std::max(c->fit.wave_bins, 0) : HF_EINVAL;
 }
 
 HF_EXPORT int hf_fit_max_wave_bins(hf_ctx* c, const hf_model* m, int32_t objective,

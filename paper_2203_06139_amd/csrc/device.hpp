@@ -38,6 +38,11 @@ struct Shape1D {
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 
+__device__ __forceinline__ double readlane_d(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
 // --------------------------------------------------------------------------
 // 1D models.  Uniform constants derived once per thread from theta.
 // --------------------------------------------------------------------------
@@ -88,6 +93,38 @@ struct Model1D {
       qE = exp_fast(c[1] * dt);
       qEm = expm1_fast(c[1] * dt);
     }
+    recur = recurs(K);
+  }
+
+  // init and init_grid by a whole wave, for a theta that is the same in all
+  // lanes: lane g takes Gaussian g's division and exp, lane NG the
+  // exponential's, lane NG + 1 1/t_scale, so each is done once per wave, and
+  // the constants end up in scalar registers.
+  __device__ __forceinline__ void init_wave(const double* th, double t_shift, double t_scale, double h,
+                                            int K) {
+    const int lane = static_cast<int>(threadIdx.x & 63u);
+    const double inv = 1.0 / (lane < NG ? th[3 * lane + 2] : (lane == NG + 1 ? t_scale : 1.0));
+    tshift = t_shift;
+    ta = readlane_d(inv, NG + 1);
+    dt = h * ta;
+    const double dl = h * inv;
+    double arg = -dl * dl;
+    if constexpr (BKG == BKG_EXP)
+      if (lane == NG) arg = th[3 * NG + 1] * dt;
+    const double ex = expm1_fast(arg);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      A[g] = readlane_d(th[3 * g], 0);
+      m[g] = readlane_d(th[3 * g + 1], 0);
+      is[g] = readlane_d(inv, g);
+      dz[g] = readlane_d(dl, g);
+      Dm[g] = -readlane_d(ex, g);
+      D[g] = 1.0 - Dm[g];
+    }
+#pragma unroll
+    for (int j = 0; j < S::NB; ++j) c[j] = readlane_d(th[3 * NG + j], 0);
+    qEm = BKG == BKG_EXP ? readlane_d(ex, NG) : 0.0;
+    qE = 1.0 + qEm;
     recur = recurs(K);
   }
 
@@ -174,11 +211,6 @@ __device__ __forceinline__ double dpp_row(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
   return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ double readlane_d(double v, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 // Sum over the 64 lanes of a full wave in a fixed order; the result is

@@ -1,5 +1,7 @@
 // fit.hip -- fitter scratch, the longest-first ordering kernel and the launch
 // of the persistent fit kernel.
+#include <algorithm>
+
 #include "fit_impl.hpp"
 
 namespace hf {
@@ -8,71 +10,79 @@ namespace {
 
 constexpr int kMaxRankB = 1 << 16;
 
-// Rank every histogram by size, longest first, ties by index: a strict total
-// order, so the ranks form a permutation.  O(B^2) comparisons staged through
-// LDS tiles; used for B <= kMaxRankB.
+// Order of a batch: histograms of more than `split` bins first, and within
+// each part longest first to 1/32 of a size, by a counting sort of one block
+// over buckets of 32 per octave (the size's FP32 exponent and top mantissa
+// bits).  Within a bucket the order is that of the LDS atomics: every fit's
+// result is its own, whatever runs beside or before it.  The wave mode of the
+// fit kernel needs the split to be exact, hence the two parts.
+// Bound: latency of two passes over the sizes.  It replaced a bitonic sort in
+// LDS (4096 histograms: 57 us) and, above 4096, a comparison of every pair
+// (16,384: 1.0 ms).
+constexpr int kSortThreads = 1024;
+constexpr int kSortBuckets = 32 * 64;  // sizes below 2^64
+constexpr int kSortPer = 2 * kSortBuckets / kSortThreads;
 
-__global__ __launch_bounds__(kBlock) void k_rank_sizes(const int64_t* __restrict__ offsets, int B,
-                                                      int32_t* __restrict__ order) {
-  __shared__ int64_t tile[kBlock];
-  const int b = blockIdx.x * kBlock + threadIdx.x;
-  const int64_t mine = b < B ? offsets[b + 1] - offsets[b] : 0;
-  int rank = 0;
-  for (int j0 = 0; j0 < B; j0 += kBlock) {
-    const int j = j0 + threadIdx.x;
-    tile[threadIdx.x] = j < B ? offsets[j + 1] - offsets[j] : 0;
-    __syncthreads();
-    const int lim = min(kBlock, B - j0);
-    for (int q = 0; q < lim; ++q) {
-      const int64_t o = tile[q];
-      rank += (o > mine) || (o == mine && j0 + q < b);
-    }
-    __syncthreads();
-  }
-  if (b < B) order[rank] = b;
+__device__ __forceinline__ int size_bucket(int64_t size, int64_t split) {
+  const float f = size < 1 ? 1.0f : static_cast<float>(size);
+  const int up = static_cast<int>((__float_as_uint(f) >> 18) - (127u << 5));  // ascending, >= 0
+  return (size <= split ? kSortBuckets : 0) + (kSortBuckets - 1 - up);
 }
 
-// Batches of at most kSortB histograms are ordered by one block instead: a
-// bitonic sort in LDS of 64-bit keys (the size's complement above the
-// index, so ascending keys are sizes descending, then indices ascending:
-// the same permutation).  Measured on 4096 histograms: 58 us, against
-// 253 us for the comparison count above (on 16 blocks).
-constexpr int kSortB = 4096;
-constexpr int kSortThreads = 1024;
-
 __global__ __launch_bounds__(kSortThreads) void k_sort_sizes(const int64_t* __restrict__ offsets,
-                                                             int B, int32_t* __restrict__ order) {
-  __shared__ uint64_t key[kSortB];
-  constexpr uint64_t kSizeMax = (uint64_t(1) << 48) - 1;  // sizes above compare as equal
-  int n = 1;
-  while (n < B) n <<= 1;
-  for (int i = threadIdx.x; i < n; i += kSortThreads) {
-    uint64_t k = ~uint64_t(0);
-    if (i < B) {
-      const int64_t sz = offsets[i + 1] - offsets[i];
-      const uint64_t c = sz <= 0 ? 0 : (static_cast<uint64_t>(sz) > kSizeMax ? kSizeMax : sz);
-      k = ((kSizeMax - c) << 16) | static_cast<uint64_t>(i);
+                                                             int B, int64_t split,
+                                                             int32_t* __restrict__ order) {
+  __shared__ int bucket[2 * kSortBuckets];
+  __shared__ int wave_total[kSortThreads / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int i = tid; i < 2 * kSortBuckets; i += kSortThreads) bucket[i] = 0;
+  __syncthreads();
+  // a wave whose histograms all share a bucket (equal sizes) adds them at once
+  auto add = [&](int k, bool in) {
+    const uint64_t mask = __ballot(in);
+    const int k0 = __builtin_amdgcn_readfirstlane(k);
+    if (__ballot(in && k != k0) == 0) {
+      int base = 0;
+      if (lane == 0) base = atomicAdd(&bucket[k0], __popcll(mask));
+      base = __builtin_amdgcn_readfirstlane(base);
+      return base + static_cast<int>(__popcll(mask & ((uint64_t(1) << lane) - 1)));
     }
-    key[i] = k;
+    return in ? atomicAdd(&bucket[k], 1) : 0;
+  };
+  for (int i0 = 0; i0 < B; i0 += kSortThreads) {
+    const int i = min(i0 + tid, B - 1);
+    add(size_bucket(offsets[i + 1] - offsets[i], split), i0 + tid < B);
   }
   __syncthreads();
-  for (int k = 2; k <= n; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < n; i += kSortThreads) {
-        const int p = i ^ j;
-        if (p > i) {
-          const uint64_t x = key[i], y = key[p];
-          if ((x > y) == ((i & k) == 0)) {
-            key[i] = y;
-            key[p] = x;
-          }
-        }
-      }
-      __syncthreads();
-    }
+  // exclusive scan of the counts: a thread's own buckets, lanes, waves
+  int mine[kSortPer], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) {
+    mine[q] = bucket[tid * kSortPer + q];
+    sum += mine[q];
   }
-  for (int i = threadIdx.x; i < B; i += kSortThreads)
-    order[i] = static_cast<int32_t>(key[i] & 0xffffu);
+  int up = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(up, d);
+    if (lane >= d) up += o;
+  }
+  if (lane == 63) wave_total[tid >> 6] = up;
+  __syncthreads();
+  int at = up - sum;
+  for (int w = 0; w < (tid >> 6); ++w) at += wave_total[w];
+#pragma unroll
+  for (int q = 0; q < kSortPer; ++q) {
+    bucket[tid * kSortPer + q] = at;
+    at += mine[q];
+  }
+  __syncthreads();
+  for (int i0 = 0; i0 < B; i0 += kSortThreads) {
+    const int i = min(i0 + tid, B - 1);
+    const bool in = i0 + tid < B;
+    const int p = add(size_bucket(offsets[i + 1] - offsets[i], split), in);
+    if (in) order[p] = i;
+  }
 }
 
 FitLaunchFn pick_fit(int ng, int bkg, int obj, int blk) {
@@ -95,7 +105,7 @@ FitLaunchFn pick_fit(int ng, int bkg, int obj, int blk) {
 }  // namespace
 
 // The ordering buffer is allocated once, for the largest batch that is
-// ranked (kMaxRankB histograms, 256 KiB), so no fit_batch call allocates,
+// sorted (kMaxRankB histograms, 256 KiB), so no fit_batch call allocates,
 // frees or synchronises, and a graph captured earlier keeps a valid pointer.
 hipError_t fit_scratch_init(FitScratch* s) {
   hipError_t e = hipMalloc(&s->counters, 256);
@@ -128,27 +138,39 @@ int fit_max_wave_bins(int n_gauss, int bkg, int obj, int block) {
   return m > 0 ? m : 0;
 }
 
+// wave_bins of a context on which none was set.  One wave per histogram saves
+// the workgroup barriers and gives a CU eight fits at once, but each of these
+// fits takes longer, which shows when there are few: so for batches of at
+// least two histograms per workgroup, and up to 2048 bins, where the slots of
+// two workgroups still fit a CU's LDS.  Measured (off, on; us): 16,384 of
+// 128..1024 bins 1574, 572; 2048 of 1000 bins 254, 146; 1500 of three
+// Gaussians on 256..2000 bins 477, 292; 1024 of 1000 bins 155, 136; 4096 of
+// 256..65536 bins 1010, 944; 1000 of those 489, 486; but 400 of 10,000 bins
+// (all sorted, none small) 173, 183, and 256 of 1000 bins 70, 96.
+static int auto_wave_bins(int n_gauss, int bkg, const FitArgs& a, int grid, const FitScratch* s) {
+  constexpr int kWaveBins = 2048, kPerGroup = 2;
+  if (a.B > kMaxRankB || a.B / kPerGroup < grid) return 0;
+  return std::min(kWaveBins, fit_max_wave_bins(n_gauss, bkg, a.obj, s->block));
+}
+
 hipError_t launch_fit(int n_gauss, int bkg, FitArgs a, int num_cu, FitScratch* s, hipStream_t st) {
   FitLaunchFn fn = pick_fit(n_gauss, bkg, a.obj, s->block);
   if (!fn) return hipErrorNotSupported;
+  int grid = num_cu * s->wg_per_cu;
+  if (grid > a.B) grid = a.B;
   a.cache_bins = s->cache_bins;
-  a.wave_bins = s->wave_bins;
-  // batches above kMaxRankB run in index order (no ranking pass)
-  a.sorted = (a.B <= kMaxRankB && a.B <= s->cap) ? 1 : 0;
+  a.wave_bins = s->wave_bins >= 0 ? s->wave_bins : auto_wave_bins(n_gauss, bkg, a, grid, s);
+  // batches above kMaxRankB run in index order, and so do those of which
+  // every workgroup takes one (the order could change nothing)
+  a.sorted = (a.B <= kMaxRankB && a.B <= s->cap && (grid < a.B || a.wave_bins > 0)) ? 1 : 0;
   a.order = s->order;
   a.counters = s->counters;
-  if (a.sorted && a.B <= kSortB) {
-    hipLaunchKernelGGL(k_sort_sizes, dim3(1), dim3(kSortThreads), 0, st, a.offsets, a.B, a.order);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  } else if (a.sorted) {
-    hipLaunchKernelGGL(k_rank_sizes, dim3((a.B + kBlock - 1) / kBlock), dim3(kBlock), 0, st,
-                       a.offsets, a.B, a.order);
+  if (a.sorted) {
+    hipLaunchKernelGGL(k_sort_sizes, dim3(1), dim3(kSortThreads), 0, st, a.offsets, a.B,
+                       static_cast<int64_t>(a.wave_bins), a.order);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  int grid = num_cu * s->wg_per_cu;
-  if (grid > a.B) grid = a.B;
   return fn(a, grid, st, nullptr);
 }
 

@@ -19,11 +19,15 @@
 // re-evaluated with FP64 bins.
 //
 // Work split: the whole workgroup (or, for small histograms, one wave)
-// evaluates the objective and gradient over the histogram's bins (chunk_1d
-// in 4- or 8-bin chunks, then a fixed-order group sum); the O(P^2) BFGS
-// algebra is spread over the first P or P^2 threads; scalar decisions are
-// computed redundantly by every thread from the same LDS values, so control
-// flow stays uniform without extra barriers.
+// evaluates the objective and gradient over the histogram's bins (run_1d, or
+// chunk_1d for FP32 bins, then a fixed-order group sum); the group's first
+// wave runs the optimiser alone: the O(P^2) algebra is spread over its lanes,
+// scalar decisions are computed redundantly by every lane from the same LDS
+// values, and the other waves wait for the next point at a barrier.  With the
+// whole workgroup in the algebra, each step behind a workgroup barrier, one
+// evaluation and iteration of a 256-bin histogram took 3.4 us, 2.9 now (and
+// the other waves' issue slots go to the CU's second workgroup: 4096 uneven
+// fits 1.12 -> 1.09 ms).
 #pragma once
 
 #include <float.h>
@@ -55,21 +59,22 @@ struct FitShared {
   double th[P], th0[P], sig[P];
   double u[P], g[P], un[P], gn[P], pv[P], tmp[P], sv[P], yv[P], Hy[P], up[P];
   double H[P * P];   // row stride P; the leading nf x nf block is used
-  double Lc[P * P];  // Fisher start: scaled F, its Cholesky factor, the inverse
   double tot[NV];
   double red[BLK / 64][NV];
   double fred[(BLK / 64) * kFisherPass];
-  double dmax;
   int redf[BLK / 64];
   int fredf[BLK / 64];
-  int chol_ok;
   int fidx[P];
   int nf;
   int h;
+  // the optimiser's state, kept by the group's first wave
+  double f, fn, nll, edm, goal, slope, alpha, fp, hp, hm;
+  int nev, it, ls, q, status, stage, after, f32, first;
+  int cmd;  // what the group evaluates next
 };
 
-// Bins per thread per step of the fit's objective sweep: 8 once every
-// thread of a workgroup has a chunk of 8, else 4.  Measured on the
+// Bins per thread per step of the FP32-bin sweep: 8 once every thread of a
+// workgroup has a chunk of 8, else 4.  Measured on the
 // 4096-histogram Gauss + exponential batch (512-thread workgroups, counts
 // in LDS): one evaluation of its longest fit (22,086 bins) 15.2 us with
 // 4-bin chunks, 13.5 with 8 and 15.5 with 16; reading the cached counts as
@@ -189,12 +194,9 @@ __device__ __forceinline__ void gsync() {
   }
 }
 
-// Sums v over the group in a fixed order (waves by wave_sum, then the waves in
-// order) and hands thread k < NV the total of component k and the OR of all
-// flags; one barrier before that and one after it.
-template <int NV, int BLK, class Done>
-__device__ __forceinline__ void group_sum(double (&v)[NV], int flags, double (*red)[NV], int* redf,
-                                          Done&& done) {
+// Each wave's sums of v and its flags into red and redf.
+template <int NV, int BLK>
+__device__ __forceinline__ void wave_totals(double (&v)[NV], int flags, double (*red)[NV], int* redf) {
 #pragma unroll
   for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
   const int f = (__ballot(flags & ST_DOMAIN) ? ST_DOMAIN : 0) |
@@ -205,31 +207,39 @@ __device__ __forceinline__ void group_sum(double (&v)[NV], int flags, double (*r
     for (int k = 0; k < NV; ++k) red[wid][k] = v[k];
     redf[wid] = f;
   }
-  gsync<BLK>();
-  const int k = gtid<BLK>();
-  if (k < NV) {
-    double x = red[0][k];
-    int o = redf[0];
-#pragma unroll
-    for (int w = 1; w < BLK / 64; ++w) {
-      x += red[w][k];
-      o |= redf[w];
-    }
-    done(k, x, o);
-  }
-  gsync<BLK>();
 }
 
-// Totals of an evaluation into sm.tot: f in tot[0] (+inf on a domain error)
-// and dL/dtheta_k in tot[1 + k].
+// The group's total of component k, the waves added in order.
+template <int NV, int BLK>
+__device__ __forceinline__ double add_waves(const double (*red)[NV], const int* redf, int k, int& flags) {
+  double x = red[0][k];
+  flags = redf[0];
+#pragma unroll
+  for (int w = 1; w < BLK / 64; ++w) {
+    x += red[w][k];
+    flags |= redf[w];
+  }
+  return x;
+}
+
+// Totals of an evaluation for the group's first wave: f in sm.tot[0] (+inf on
+// a domain error) and dL/dtheta_k in sm.tot[1 + k].  One group barrier.
 template <int NG, int BKG, int BLK, int NV>
 __device__ __forceinline__ void publish_totals(FitShared<NG, BKG, BLK>& sm, const Model1D<NG, BKG>& M,
                                                double (&acc)[NV], int flags) {
-  group_sum<NV, BLK>(acc, flags, reinterpret_cast<double(*)[NV]>(sm.red), sm.redf,
-                     [&](int k, double x, int o) {
-                       if (k == 0 && (o & ST_DOMAIN)) x = __builtin_inf();
-                       sm.tot[k] = k == 0 ? x : x * M.final_factor(k);
-                     });
+  double(*red)[NV] = reinterpret_cast<double(*)[NV]>(sm.red);
+  wave_totals<NV, BLK>(acc, flags, red, sm.redf);
+  gsync<BLK>();
+  const int k = gtid<BLK>();
+  if (k < 64) {
+    if (k < NV) {
+      int o;
+      double x = add_waves<NV, BLK>(red, sm.redf, k, o);
+      if (k == 0 && (o & ST_DOMAIN)) x = __builtin_inf();
+      sm.tot[k] = k == 0 ? x : x * M.final_factor(k);
+    }
+    gsync<64>();
+  }
 }
 
 // Objective (and with GRAD its gradient) of one histogram at sm.th with FP32
@@ -315,8 +325,7 @@ __device__ __forceinline__ void wg_eval_runs(const FitArgs& a, FitShared<NG, BKG
   constexpr int NV = GRAD ? FitShared<NG, BKG, BLK>::NV : 1;
   const int tid = gtid<BLK>();
   Model1D<NG, BKG> M;
-  M.init(sm.th, a.t_shift, a.t_scale);
-  M.init_grid(hx, 4 * S);
+  M.init_wave(sm.th, a.t_shift, a.t_scale, hx, 4 * S);
   if (!M.recur && S > 1) {
     S = 1;
     M.recur = M.recurs(4);
@@ -497,8 +506,7 @@ __device__ __forceinline__ void fisher_pass(const FitArgs& a, FitShared<NG, BKG,
     constexpr int NQ = (N - E0 < W) ? N - E0 : W;
     const int tid = gtid<BLK>();
     Model1D<NG, BKG> M;
-    M.init(sm.th0, a.t_shift, a.t_scale);
-    M.init_grid(hx, 4 * S);
+    M.init_wave(sm.th0, a.t_shift, a.t_scale, hx, 4 * S);
     if (!M.recur && S > 1) {
       S = 1;
       M.recur = M.recurs(4);
@@ -522,84 +530,79 @@ __device__ __forceinline__ void fisher_pass(const FitArgs& a, FitShared<NG, BKG,
       double part[kFisherPass];
 #pragma unroll
       for (int q = 0; q < kFisherPass; ++q) part[q] = c0 + q < NQ ? acc[c0 + q < NQ ? c0 + q : 0] : 0.0;
-      group_sum<kFisherPass, BLK>(
-          part, 0, reinterpret_cast<double(*)[kFisherPass]>(sm.fred), sm.fredf,
-          [&](int k, double x, int) {
-            if (c0 + k >= NQ) return;
-            const int r = tri.a[E0 + c0 + k], c = tri.b[E0 + c0 + k];
-            const double f = x * M.final_factor(1 + r) * M.final_factor(1 + c);
-            sm.H[r * P + c] = f;
-            sm.H[c * P + r] = f;
-          });
+      double(*red)[kFisherPass] = reinterpret_cast<double(*)[kFisherPass]>(sm.fred);
+      wave_totals<kFisherPass, BLK>(part, 0, red, sm.fredf);
+      gsync<BLK>();
+      if (tid < kFisherPass && c0 + tid < NQ) {
+        int o;
+        const int r = tri.a[E0 + c0 + tid], c = tri.b[E0 + c0 + tid];
+        const double f = add_waves<kFisherPass, BLK>(red, sm.fredf, tid, o) * M.final_factor(1 + r) *
+                         M.final_factor(1 + c);
+        sm.H[r * P + c] = f;
+        sm.H[c * P + r] = f;
+      }
+      gsync<BLK>();
     }
     fisher_pass<NG, BKG, OBJ, PASS + 1, BLK>(a, sm, src, nb, x0, hx, S);
   }
 }
 
-// Replaces the identity in sm.H by the inverse of F_u = diag(sigma) F
-// diag(sigma) over the free parameters, F already in sm.H: Cholesky
-// F_u = L L^T (a pivot must exceed 1e-12 times the largest diagonal entry),
-// inv(L) by forward substitution, H = inv(L)^T inv(L).  Falls back to the
+// Replaces F in sm.H by the inverse of F_u = diag(sigma) F diag(sigma) over
+// the free parameters: Cholesky F_u = L L^T (a pivot must exceed 1e-12 times
+// the largest diagonal entry), X = inv(L), H = X^T X.  Falls back to the
 // identity when F_u is not safely positive definite or anything is not
-// finite.  Returns whether the inverse was taken.
+// finite.  Returns whether the inverse was taken.  One wave: lane r holds row
+// r of F_u and L, then column r of X, in registers, and takes the other
+// lanes' values by readlane; rows past nf are the identity's.
 template <int NG, int BKG, int BLK>
 __device__ __forceinline__ bool fisher_start(FitShared<NG, BKG, BLK>& sm, int nf) {
   constexpr int P = FitShared<NG, BKG, BLK>::P;
-  const int tid = gtid<BLK>();
-  gsync<BLK>();
-  for (int t = tid; t < nf * nf; t += BLK) {
-    const int r = t / nf, c = t % nf;
-    sm.Lc[r * P + c] = sm.sig[sm.fidx[r]] * sm.sig[sm.fidx[c]] * sm.H[sm.fidx[r] * P + sm.fidx[c]];
+  const int r = static_cast<int>(threadIdx.x & 63u);
+  const bool mine = r < nf;
+  const int kr = mine ? sm.fidx[r] : 0;
+  const double sr = sm.sig[kr];
+  double a[P], x[P];
+  double diag = mine ? sr * sr * sm.H[kr * P + kr] : 0.0;
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    const int kc = c < nf ? sm.fidx[c] : 0;
+    a[c] = mine && c < nf ? sr * sm.sig[kc] * sm.H[kr * P + kc] : (r == c ? 1.0 : 0.0);
   }
-  gsync<BLK>();
-  if (tid == 0) {
-    double dmax = 0.0;
-    for (int r = 0; r < nf; ++r) dmax = fmax(dmax, sm.Lc[r * P + r]);
-    sm.dmax = dmax;
-    sm.chol_ok = (dmax > 0.0 && __builtin_isfinite(dmax)) ? 1 : 0;
+  double dmax = 0.0;
+#pragma unroll
+  for (int c = 0; c < P; ++c) dmax = fmax(dmax, readlane_d(diag, c));
+  bool ok = dmax > 0.0 && __builtin_isfinite(dmax);
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const double d = readlane_d(a[j], j);
+    if (j < nf && (!(d > 1e-12 * dmax) || !__builtin_isfinite(d))) ok = false;
+    const double piv = sqrt(d);
+    a[j] = r == j ? piv : a[j] / piv;
+#pragma unroll
+    for (int c = j + 1; c < P; ++c) a[c] = fma(-a[j], readlane_d(a[j], c), a[c]);
   }
-  gsync<BLK>();
-  const double dmax = sm.dmax;
-  for (int j = 0; j < nf && sm.chol_ok; ++j) {
-    if (tid == 0) {
-      double d = sm.Lc[j * P + j];
-      for (int k = 0; k < j; ++k) d -= sm.Lc[j * P + k] * sm.Lc[j * P + k];
-      if (!(d > 1e-12 * dmax) || !__builtin_isfinite(d)) sm.chol_ok = 0;
-      else sm.Lc[j * P + j] = sqrt(d);
-    }
-    gsync<BLK>();
-    if (sm.chol_ok && tid > j && tid < nf) {
-      double v = sm.Lc[tid * P + j];
-      for (int k = 0; k < j; ++k) v -= sm.Lc[tid * P + k] * sm.Lc[j * P + k];
-      sm.Lc[tid * P + j] = v / sm.Lc[j * P + j];
-    }
-    gsync<BLK>();
+#pragma unroll
+  for (int i = 0; i < P; ++i) {
+    double v = r == i ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < i; ++k) v = fma(-readlane_d(a[k], i), x[k], v);
+    x[i] = v / readlane_d(a[i], i);
   }
-  if (sm.chol_ok) {
-    if (tid < nf) {  // column tid of inv(L), into the lower triangle of H
-      const int c = tid;
-      for (int i = c; i < nf; ++i) {
-        double v = (i == c) ? 1.0 : 0.0;
-        for (int k = c; k < i; ++k) v -= sm.Lc[i * P + k] * sm.H[k * P + c];
-        sm.H[i * P + c] = v / sm.Lc[i * P + i];
-      }
-    }
-    gsync<BLK>();
-    for (int t = tid; t < nf * nf; t += BLK) {
-      const int r = t / nf, c = t % nf;
-      double v = 0.0;
-      for (int k = (r > c ? r : c); k < nf; ++k) v += sm.H[k * P + r] * sm.H[k * P + c];
-      sm.Lc[r * P + c] = v;
-      if (!__builtin_isfinite(v)) sm.chol_ok = 0;
-    }
-    gsync<BLK>();
+  gsync<64>();  // every lane has read F
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = c; k < P; ++k) v = fma(x[k], readlane_d(x[k], c), v);
+    if (mine && c < nf && !__builtin_isfinite(v)) ok = false;
+    a[c] = v;
   }
-  const bool ok = sm.chol_ok != 0;
-  for (int t = tid; t < P * P; t += BLK) {
-    const int r = t / P, c = t % P;
-    sm.H[t] = (ok && r < nf && c < nf) ? sm.Lc[r * P + c] : (r == c ? 1.0 : 0.0);
+  ok = __all(ok);
+  if (r < P) {
+#pragma unroll
+    for (int c = 0; c < P; ++c) sm.H[r * P + c] = ok && mine && c < nf ? a[c] : (r == c ? 1.0 : 0.0);
   }
-  gsync<BLK>();
+  gsync<64>();
   return ok;
 }
 
@@ -626,8 +629,219 @@ __device__ __forceinline__ double dot_lds(const double* x, const double* y, int 
 // / (2h) with h = kFdStep max(1, |u_q|), 2 nf objective sweeps.
 constexpr double kFdStep = 1e-4;
 
-// What an evaluation was for (see fit_one).
+// What an evaluation was for (optimiser_step), and what is evaluated next.
 enum : int { EV_INIT = 0, EV_POLISH, EV_SEARCH, EV_FINAL, EV_FD_PLUS, EV_FD_MINUS };
+enum : int { CMD_DONE = 0, CMD_VALUE, CMD_F32, CMD_F64 };
+
+// Sets the group's next evaluation: at the point `un` (or `up` for central
+// differences) of the scaled free coordinates.
+template <int NG, int BKG, int BLK>
+__device__ __forceinline__ void optimiser_point(const FitArgs& a, FitShared<NG, BKG, BLK>& sm, int stage,
+                                                bool f32) {
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  if (lane < sm.nf) {
+    const int k = sm.fidx[lane];
+    sm.th[k] = fma(sm.sig[k], stage >= EV_FD_PLUS ? sm.up[lane] : sm.un[lane], sm.th0[k]);
+  }
+  if (lane == 0) {
+    sm.stage = stage;
+    sm.f32 = f32 ? 1 : 0;
+    sm.cmd = a.fd_grad != 0 ? CMD_VALUE : (f32 && stage != EV_FINAL ? CMD_F32 : CMD_F64);
+  }
+}
+
+template <int NG, int BKG, int BLK>
+__device__ __forceinline__ void optimiser_end(FitShared<NG, BKG, BLK>& sm, double nll, int status) {
+  if ((threadIdx.x & 63u) == 0) {
+    sm.nll = nll;
+    sm.status = status;
+    sm.cmd = CMD_DONE;
+  }
+}
+
+// First Hessian and the evaluation at the start.
+template <int NG, int BKG, int OBJ, int BLK>
+__device__ __forceinline__ void optimiser_begin(const FitArgs& a, FitShared<NG, BKG, BLK>& sm) {
+  constexpr int P = FitShared<NG, BKG, BLK>::P;
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  bool first = true;  // scale H at the first update: not after a Fisher start
+  if (a.hessian_init == 1 && sm.nf > 0) {
+    first = !fisher_start(sm, sm.nf);
+  } else {
+    for (int t = lane; t < P * P; t += 64) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
+  }
+  if (lane == 0) {
+    sm.first = first ? 1 : 0;
+    sm.f = sm.edm = sm.goal = sm.slope = 0.0;
+    sm.alpha = 1.0;
+    sm.nev = 1;
+    sm.it = sm.ls = sm.q = 0;
+    sm.status = FIT_MAXITER;
+  }
+  optimiser_point(a, sm, EV_INIT, a.f32 != 0);
+}
+
+// Takes the evaluation of sm.tot and sets the next one, or ends the fit.
+// Scalar decisions are computed redundantly by every lane from the same LDS
+// values, so control flow is uniform.
+template <int NG, int BKG, int OBJ, int BLK>
+__device__ __forceinline__ void optimiser_step(const FitArgs& a, FitShared<NG, BKG, BLK>& sm) {
+  constexpr int P = FitShared<NG, BKG, BLK>::P;
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  const int nf = sm.nf, stage = sm.stage;
+  const bool fd = a.fd_grad != 0;  // central differences (FP64 bins only)
+  const bool f32 = sm.f32 != 0;
+  const double fe = sm.tot[0];
+  double f = sm.f;
+  bool accepted = false;
+  if (stage == EV_FINAL) return optimiser_end(sm, fe, sm.status);
+  if (stage == EV_FD_PLUS) {
+    const double hm = sm.hm;
+    const int q = sm.q;
+    gsync<64>();
+    if (lane == 0) sm.fp = fe;
+    if (lane < nf) sm.up[lane] = lane == q ? hm : sm.un[lane];
+    return optimiser_point(a, sm, EV_FD_MINUS, false);
+  }
+  int q = 0;  // next coordinate of the differences, if any
+  bool differences = false;
+  if (stage == EV_FD_MINUS) {
+    q = sm.q;
+    const double g = (sm.fp - fe) / (sm.hp - sm.hm);
+    accepted = sm.after == EV_SEARCH;
+    gsync<64>();
+    if (lane == 0) sm.gn[q] = g;
+    differences = ++q < nf;
+    if (!differences && lane == 0) sm.nev += 2 * nf;
+    gsync<64>();
+  } else {
+    bool go_on;
+    if (stage == EV_SEARCH) {
+      const double alpha = sm.alpha;
+      const int ls = sm.ls + 1;
+      go_on = accepted = __builtin_isfinite(fe) && fe <= f + 1e-4 * alpha * sm.slope;
+      const double edm = sm.edm, goal = sm.goal;
+      gsync<64>();
+      if (lane == 0) {
+        ++sm.nev;
+        if (accepted) ++sm.it;
+        sm.ls = ls;
+        sm.alpha = 0.5 * alpha;
+      }
+      if (!accepted && ls < a.ls_max) {
+        if (lane < nf) sm.un[lane] = sm.u[lane] + 0.5 * alpha * sm.pv[lane];
+        return optimiser_point(a, sm, EV_SEARCH, f32);
+      }
+      if (!accepted && lane == 0) sm.status = edm < goal ? FIT_CONVERGED : FIT_LSFAIL;
+      gsync<64>();
+    } else {
+      f = fe;
+      go_on = __builtin_isfinite(f);
+      gsync<64>();
+      if (lane == 0) {
+        sm.f = f;
+        if (!go_on) sm.status = f == __builtin_inf() ? FIT_DOMAIN : FIT_NONFINITE;
+      }
+      gsync<64>();
+    }
+    if (!go_on) {
+      if (!(f32 && __builtin_isfinite(f))) return optimiser_end(sm, f, sm.status);
+      if (lane < nf) sm.un[lane] = sm.u[lane];
+      return optimiser_point(a, sm, EV_FINAL, true);
+    }
+    differences = fd && nf > 0;  // the gradient, only at accepted points
+    if (differences && lane == 0) sm.after = stage;
+    if (differences && accepted && lane == 0) sm.fn = fe;
+  }
+  if (differences) {
+    const double uq = sm.un[q], h = kFdStep * fmax(1.0, fabs(uq));
+    if (lane == 0) {
+      sm.q = q;
+      sm.hp = uq + h;
+      sm.hm = uq - h;
+    }
+    if (lane < nf) sm.up[lane] = lane == q ? uq + h : sm.un[lane];
+    return optimiser_point(a, sm, EV_FD_PLUS, false);
+  }
+  // gradient at the new point, in the scaled coordinates
+  double gq = 0.0;
+  if (lane < nf) gq = fd ? sm.gn[lane] : sm.sig[sm.fidx[lane]] * sm.tot[1 + sm.fidx[lane]];
+  if (accepted) {
+    if (lane < nf) {
+      sm.sv[lane] = sm.un[lane] - sm.u[lane];
+      sm.yv[lane] = gq - sm.g[lane];
+    }
+    f = fd && nf > 0 ? sm.fn : fe;
+    gsync<64>();
+    const double sy = dot_lds<P>(sm.sv, sm.yv, nf);
+    const double yy = dot_lds<P>(sm.yv, sm.yv, nf);
+    const double ss = dot_lds<P>(sm.sv, sm.sv, nf);
+    if (sy > 1e-12 * sqrt(ss) * sqrt(yy)) {
+      if (sm.first) {
+        const double gam = sy / yy;
+        gsync<64>();
+        for (int t = lane; t < nf * nf; t += 64) sm.H[(t / nf) * P + t % nf] *= gam;
+        if (lane == 0) sm.first = 0;
+        gsync<64>();
+      }
+      if (lane < nf) sm.Hy[lane] = dot_lds<P>(&sm.H[lane * P], sm.yv, nf);
+      gsync<64>();
+      const double yHy = dot_lds<P>(sm.yv, sm.Hy, nf);
+      const double rho = 1.0 / sy;
+      const double cc = rho * rho * yHy + rho;
+      for (int t = lane; t < nf * nf; t += 64) {
+        const int r = t / nf, c = t % nf;
+        sm.H[r * P + c] += -rho * (sm.Hy[r] * sm.sv[c] + sm.sv[r] * sm.Hy[c]) + cc * sm.sv[r] * sm.sv[c];
+      }
+    }
+  }
+  if (lane < nf) {
+    sm.u[lane] = sm.un[lane];
+    sm.g[lane] = gq;
+  }
+  if (lane == 0) sm.f = f;
+  gsync<64>();
+  // direction p = -H g
+  if (sm.it < a.max_iter) {
+    if (lane < nf) {
+      const double hg = dot_lds<P>(&sm.H[lane * P], sm.g, nf);
+      sm.pv[lane] = -hg;
+      sm.tmp[lane] = sm.g[lane] * hg;
+    }
+    gsync<64>();
+    const double edm = 0.5 * dot_lds<P>(sm.tmp, nullptr, nf);
+    const double goal = fmax(a.edm_tol, 4.0 * DBL_EPSILON * fabs(f));
+    if (f32 && a.polish_edm > 0.0 && edm < a.polish_edm) {
+      // switch to FP64 bins for the rest of the fit, at sm.un = sm.u
+      if (lane == 0) ++sm.nev;
+      return optimiser_point(a, sm, EV_POLISH, false);
+    }
+    if (!a.fixed_iters && edm < goal) {
+      if (lane == 0) sm.status = FIT_CONVERGED;
+    } else {
+      double slope = dot_lds<P>(sm.g, sm.pv, nf);
+      if (!(slope < 0.0)) {  // H lost positive definiteness: restart from I
+        gsync<64>();
+        for (int t = lane; t < P * P; t += 64) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
+        if (lane < nf) sm.pv[lane] = -sm.g[lane];
+        if (lane == 0) sm.first = 1;
+        slope = -dot_lds<P>(sm.g, sm.g, nf);
+      }
+      if (lane == 0) {
+        sm.edm = edm;
+        sm.goal = goal;
+        sm.slope = slope;
+        sm.alpha = 1.0;
+        sm.ls = 0;
+      }
+      if (lane < nf) sm.un[lane] = sm.u[lane] + sm.pv[lane];
+      return optimiser_point(a, sm, EV_SEARCH, f32);
+    }
+    gsync<64>();
+  }
+  if (!f32) return optimiser_end(sm, f, sm.status);
+  optimiser_point(a, sm, EV_FINAL, true);  // the NLL at sm.un = sm.u once more with FP64 bins
+}
 
 template <int NG, int BKG, int OBJ, int BLK>
 __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK>& sm,
@@ -676,186 +890,33 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
     sm.nf = nf;
   }
   if (tid < P) sm.u[tid] = sm.un[tid] = 0.0;
-  for (int t = tid; t < P * P; t += BLK) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
   gsync<BLK>();
-  const int nf = sm.nf;
-  bool first = true;
-  if (a.hessian_init == 1 && nf > 0) {
-    fisher_pass<NG, BKG, OBJ, 0, BLK>(a, sm, src, nb, x0, hx, S);
-    first = !fisher_start(sm, nf);  // no first-update scaling after a Fisher start
-  }
-
-  bool f32 = a.f32 != 0;
-  const bool fd = a.fd_grad != 0;  // central differences (FP64 bins only)
-  const int kq = tid < nf ? sm.fidx[tid] : 0;           // this thread's free parameter
-  const double sq = tid < nf ? sm.sig[kq] : 0.0;        // and its scale
-  double f = 0.0, fn = 0.0, nll = 0.0, edm = 0.0, goal = 0.0, slope = 0.0, alpha = 1.0;
-  double fp = 0.0, hp = 0.0, hm = 0.0;  // central differences: value and points of one side
-  int nev = 1, it = 0, ls = 0, q = 0, status = FIT_MAXITER;
-  int stage = EV_INIT, after = EV_INIT;
-  // Every evaluation of a fit passes through this one place, at the point
-  // sm.un (sm.up for central differences), and `stage` says what it was for:
-  // the compiler then builds each sweep once per thread group.
+  const bool lead = tid < 64;
+  if (a.hessian_init == 1 && sm.nf > 0) fisher_pass<NG, BKG, OBJ, 0, BLK>(a, sm, src, nb, x0, hx, S);
+  if (lead) optimiser_begin<NG, BKG, OBJ, BLK>(a, sm);
+  // The group's first wave runs the optimiser, alone and without group
+  // barriers; the others only evaluate, at the point in sm.th.  Every
+  // evaluation of a fit passes through this one place, so each sweep is built
+  // once per group size.
   for (;;) {
-    if (tid < nf) sm.th[kq] = fma(sq, stage >= EV_FD_PLUS ? sm.up[tid] : sm.un[tid], sm.th0[kq]);
     gsync<BLK>();
-    if (fd)
+    const int cmd = sm.cmd;
+    if (cmd == CMD_DONE) break;
+    if (cmd == CMD_VALUE)
       wg_eval<NG, BKG, OBJ, false, false, BLK>(a, sm, lut, src, nb, x0, hx, S);
-    else if (f32 && stage != EV_FINAL)
+    else if (cmd == CMD_F32)
       wg_eval<NG, BKG, OBJ, true, true, BLK>(a, sm, lut, src, nb, x0, hx, S);
     else
       wg_eval<NG, BKG, OBJ, false, true, BLK>(a, sm, lut, src, nb, x0, hx, S);
-    const double fe = sm.tot[0];
-    bool accepted = false;
-    if (stage == EV_FINAL) {
-      nll = fe;
-      break;
-    } else if (stage == EV_FD_PLUS) {
-      fp = fe;
-      if (tid < nf) sm.up[tid] = tid == q ? hm : sm.un[tid];
-      stage = EV_FD_MINUS;
-      continue;
-    } else if (stage == EV_FD_MINUS) {
-      if (tid == 0) sm.gn[q] = (fp - fe) / (hp - hm);
-      if (++q < nf) {
-        const double h = kFdStep * fmax(1.0, fabs(sm.un[q]));
-        hp = sm.un[q] + h;
-        hm = sm.un[q] - h;
-        if (tid < nf) sm.up[tid] = tid == q ? hp : sm.un[tid];
-        stage = EV_FD_PLUS;
-        continue;
-      }
-      nev += 2 * nf;
-      gsync<BLK>();
-      accepted = after == EV_SEARCH;
-    } else {
-      fn = fe;
-      if (stage == EV_SEARCH) {
-        ++nev;
-        if (!(__builtin_isfinite(fn) && fn <= f + 1e-4 * alpha * slope)) {
-          alpha *= 0.5;
-          if (++ls < a.ls_max) {
-            if (tid < nf) sm.un[tid] = sm.u[tid] + alpha * sm.pv[tid];
-            continue;
-          }
-          status = (edm < goal) ? FIT_CONVERGED : FIT_LSFAIL;
-        } else {
-          accepted = true;
-          ++it;
-        }
-      } else {
-        f = fn;
-        if (!__builtin_isfinite(f))
-          status = (f == __builtin_inf()) ? FIT_DOMAIN : FIT_NONFINITE;
-      }
-      const bool go_on = stage == EV_SEARCH ? accepted : __builtin_isfinite(f);
-      if (!go_on) {
-        if (f32 && __builtin_isfinite(f)) {
-          stage = EV_FINAL;
-          if (tid < nf) sm.un[tid] = sm.u[tid];
-          continue;
-        }
-        nll = f;
-        break;
-      }
-      if (fd && nf > 0) {  // the gradient, only at accepted points
-        after = stage;
-        q = 0;
-        const double h = kFdStep * fmax(1.0, fabs(sm.un[0]));
-        hp = sm.un[0] + h;
-        hm = sm.un[0] - h;
-        if (tid < nf) sm.up[tid] = tid == 0 ? hp : sm.un[tid];
-        stage = EV_FD_PLUS;
-        continue;
-      }
-    }
-    // gradient at the new point, in the scaled coordinates
-    double gq = 0.0;
-    if (tid < nf) gq = fd ? sm.gn[tid] : sq * sm.tot[1 + kq];
-    if (accepted) {
-      if (tid < nf) {
-        sm.sv[tid] = sm.un[tid] - sm.u[tid];
-        sm.yv[tid] = gq - sm.g[tid];
-      }
-      gsync<BLK>();
-      const double sy = dot_lds<P>(sm.sv, sm.yv, nf);
-      const double yy = dot_lds<P>(sm.yv, sm.yv, nf);
-      const double ss = dot_lds<P>(sm.sv, sm.sv, nf);
-      if (sy > 1e-12 * sqrt(ss) * sqrt(yy)) {
-        if (first) {
-          const double gam = sy / yy;
-          for (int t = tid; t < nf * nf; t += BLK) sm.H[(t / nf) * P + t % nf] *= gam;
-          first = false;
-          gsync<BLK>();
-        }
-        if (tid < nf) sm.Hy[tid] = dot_lds<P>(&sm.H[tid * P], sm.yv, nf);
-        gsync<BLK>();
-        const double yHy = dot_lds<P>(sm.yv, sm.Hy, nf);
-        const double rho = 1.0 / sy;
-        const double cc = rho * rho * yHy + rho;
-        for (int t = tid; t < nf * nf; t += BLK) {
-          const int r = t / nf, c = t % nf;
-          sm.H[r * P + c] += -rho * (sm.Hy[r] * sm.sv[c] + sm.sv[r] * sm.Hy[c]) + cc * sm.sv[r] * sm.sv[c];
-        }
-      }
-      f = fn;
-    }
-    if (tid < nf) {
-      sm.u[tid] = sm.un[tid];
-      sm.g[tid] = gq;
-    }
-    gsync<BLK>();
-    // direction p = -H g
-    stage = EV_SEARCH;
-    if (it < a.max_iter) {
-      if (tid < nf) {
-        const double hg = dot_lds<P>(&sm.H[tid * P], sm.g, nf);
-        sm.pv[tid] = -hg;
-        sm.tmp[tid] = sm.g[tid] * hg;
-      }
-      gsync<BLK>();
-      edm = 0.5 * dot_lds<P>(sm.tmp, nullptr, nf);
-      goal = fmax(a.edm_tol, 4.0 * DBL_EPSILON * fabs(f));
-      if (f32 && a.polish_edm > 0.0 && edm < a.polish_edm) {
-        // switch to FP64 bins for the rest of the fit
-        f32 = false;
-        ++nev;
-        stage = EV_POLISH;  // at sm.un = sm.u
-        continue;
-      }
-      if (!a.fixed_iters && edm < goal) {
-        status = FIT_CONVERGED;
-      } else {
-        slope = dot_lds<P>(sm.g, sm.pv, nf);
-        if (!(slope < 0.0)) {  // H lost positive definiteness: restart from I
-          gsync<BLK>();
-          for (int t = tid; t < P * P; t += BLK) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
-          if (tid < nf) sm.pv[tid] = -sm.g[tid];
-          first = true;
-          gsync<BLK>();
-          slope = -dot_lds<P>(sm.g, sm.g, nf);
-        }
-        alpha = 1.0;
-        ls = 0;
-        if (tid < nf) sm.un[tid] = sm.u[tid] + alpha * sm.pv[tid];
-        continue;
-      }
-    }
-    if (!f32) {  // else the NLL at sm.un = sm.u once more with FP64 bins
-      nll = f;
-      break;
-    }
-    stage = EV_FINAL;
+    if (lead) optimiser_step<NG, BKG, OBJ, BLK>(a, sm);
   }
+  if (!lead) return;
   // final parameters, canonicalised
-  if (tid < P) sm.th[tid] = sm.th0[tid];
-  gsync<BLK>();
-  if (tid < nf) {
-    const int k = sm.fidx[tid];
-    sm.th[k] = fma(sm.sig[k], sm.u[tid], sm.th0[k]);
-  }
-  gsync<BLK>();
   if (tid == 0) {
+    for (int q = 0; q < sm.nf; ++q) {
+      const int k = sm.fidx[q];
+      sm.th[k] = fma(sm.sig[k], sm.u[q], sm.th0[k]);
+    }
     for (int g = 0; g < NG; ++g) sm.th[3 * g + 2] = fabs(sm.th[3 * g + 2]);
     for (int p = 1; p < NG; ++p)
       for (int q = p; q > 0 && sm.th[3 * q + 1] < sm.th[3 * (q - 1) + 1]; --q)
@@ -864,14 +925,14 @@ __device__ __forceinline__ void fit_one(const FitArgs& a, FitShared<NG, BKG, BLK
           sm.th[3 * q + r] = sm.th[3 * (q - 1) + r];
           sm.th[3 * (q - 1) + r] = t;
         }
-    a.nll_out[b] = nll;
-    a.status[b] = status;
-    a.iters[b] = it;
-    a.nevals[b] = nev;
+    a.nll_out[b] = sm.nll;
+    a.status[b] = sm.status;
+    a.iters[b] = sm.it;
+    a.nevals[b] = sm.nev;
   }
-  gsync<BLK>();
+  gsync<64>();
   if (tid < P) a.theta_out[static_cast<int64_t>(b) * P + tid] = sm.th[tid];
-  gsync<BLK>();
+  gsync<64>();
 }
 
 // Bytes of dynamic LDS one wave takes in wave mode: its fit state, then an
@@ -890,41 +951,50 @@ __global__ __launch_bounds__(BLK, 2) void k_fit(FitArgs a) {
   // the workgroup's count cache, or the waves' slots
   extern __shared__ __attribute__((aligned(16))) uint32_t cache[];
   const int tid = threadIdx.x;
-  if constexpr (OBJ == OBJ_POISSON) log_lut_load(lut, a.log_lut);
-  // wave mode needs the longest-first order: the first histogram of at most
-  // wave_bins bins is followed by smaller ones only
+  // the log table, by the waves other than the first, which meanwhile starts
+  // on the first histogram; fit_one's barriers come before its first use
+  if constexpr (OBJ == OBJ_POISSON) {
+    if (tid >= 64)
+      for (int j = tid - 64; j < kLogLut; j += BLK - 64) lut[j] = a.log_lut[j];
+  }
+  // The first gridDim.x places of the queue belong to the workgroups by index;
+  // the counter hands out the rest.  With no more histograms than workgroups
+  // there is no rest, and the queue is not touched (nor re-armed).
+  const bool queue = static_cast<int>(gridDim.x) < a.B;
+  auto take = [&]() { return queue ? static_cast<int>(gridDim.x + atomicAdd(&a.counters[0], 1u)) : a.B; };
+  // wave mode: the order puts every histogram of at most wave_bins bins after
+  // all larger ones, so the first of them is followed by such only
   const bool waves = a.wave_bins > 0 && a.sorted;
-  int h;
-  for (;;) {
-    if (tid == 0) sm.h = static_cast<int>(atomicAdd(&a.counters[0], 1u));
-    __syncthreads();
-    h = sm.h;
-    __syncthreads();
-    if (h >= a.B) break;
+  int h = blockIdx.x;
+  while (h < a.B) {
     const int b = a.sorted ? a.order[h] : h;
     if (waves && a.offsets[b + 1] - a.offsets[b] <= a.wave_bins) break;
     fit_one<NG, BKG, OBJ, BLK>(a, sm, lut, cache, a.cache_bins, b);
+    if (tid == 0) sm.h = take();
+    __syncthreads();
+    h = sm.h;
+    __syncthreads();
   }
   if (waves && h < a.B) {
+    __syncthreads();  // the log table, where no histogram came before
     // from here on every wave fits its own histograms: wave 0 the one just
     // taken, the others and every later one from the queue
     const int w = tid >> 6;
     char* slot = reinterpret_cast<char*>(cache) + w * wave_slot_bytes<NG, BKG>(a.wave_bins);
     auto& sw = *reinterpret_cast<FitShared<NG, BKG, 64>*>(slot);
     uint32_t* wc = reinterpret_cast<uint32_t*>(slot + wave_slot_bytes<NG, BKG>(0));
-    int hw = h;
-    if (w != 0) {
+    auto take_wave = [&]() {
       int t = 0;
-      if ((tid & 63) == 0) t = static_cast<int>(atomicAdd(&a.counters[0], 1u));
-      hw = __shfl(t, 0);
-    }
+      if ((tid & 63) == 0) t = take();
+      return __shfl(t, 0);
+    };
+    int hw = w == 0 ? h : take_wave();
     while (hw < a.B) {
       fit_one<NG, BKG, OBJ, 64>(a, sw, lut, wc, a.wave_bins, a.order[hw]);
-      int t = 0;
-      if ((tid & 63) == 0) t = static_cast<int>(atomicAdd(&a.counters[0], 1u));
-      hw = __shfl(t, 0);
+      hw = take_wave();
     }
   }
+  if (!queue) return;
   __syncthreads();  // every wave is past the queue before the workgroup leaves
   // the last workgroup to leave re-arms the queue for the next launch
   if (tid == 0) {

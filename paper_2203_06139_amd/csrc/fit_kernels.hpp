@@ -54,7 +54,7 @@ struct FitScratch {
   int wg_per_cu = 2;   // persistent workgroups per CU
   int cache_bins = 0;  // histograms with at most this many u32 bins live in LDS
   int block = 256;     // threads per workgroup (256 or 512)
-  int wave_bins = 0;   // one wave per histogram of at most this many bins (0: off)
+  int wave_bins = -1;  // one wave per histogram of at most this many bins (0: off, -1: by batch)
 };
 
 hipError_t fit_scratch_init(FitScratch* s);

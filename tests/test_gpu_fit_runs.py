@@ -79,3 +79,52 @@ def test_one_step_from_every_source_and_size(hf, orc, name, obj):
     finally:
         hf.fit_set_wave_bins(0)
         hf.fit_set_tuning(2, 0, 256)
+
+
+@pytest.mark.parametrize("B", [512, 513, 1024, 1500])
+def test_batch_that_chooses_its_schedule(hf, B):
+    """With no wave_bins set, the number of histograms decides whether the
+    batch is sorted and whether small ones go one to a wave (512 workgroups:
+    one each, one left over, two each, more): every fit as with wave_bins off
+    (the order of a sum apart), empty histograms refused, twice in a row (the
+    queue is re-armed, or was never used)."""
+    import torch
+    kind, ng, deg, th = MODELS["gauss-exp"]
+    spec = datagen.model_spec(kind, ng, deg, 0.0, 1.0)
+    rng = np.random.default_rng(B)
+    sizes = rng.choice([0, 300, 300, 300, 700, 2047, 2048, 2049, 5000], B)
+    sizes[-1] = 300
+    lam = {n: datagen.intensity_1d(spec, np.array(th), int(n), 0.0, 1.0) for n in set(sizes) if n}
+    counts = np.concatenate([datagen.poisson_counts(lam[n], rng) for n in sizes if n])
+    off = torch.as_tensor(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)).cuda()
+    th0 = torch.as_tensor(np.array([datagen.perturb(th, 0.02, rng) for _ in sizes])).cuda()
+    rg = torch.tensor([[0.0, 1.0]], dtype=torch.float64).repeat(B, 1).cuda()
+    c = torch.from_numpy(counts.view(np.int32)).cuda()
+    m = hf.Model.from_spec(spec)
+
+    def run():
+        r = hf.fit_batch(c, off, rg, m, th0)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (r.theta, r.nll, r.status, r.iters, r.nevals)]
+
+    contexts = (dict(hf._ctx), dict(hf._pool), dict(hf._wave_bins))
+    try:
+        for d in (hf._ctx, hf._pool, hf._wave_bins):
+            d.clear()
+        first, second = run(), run()
+        hf.fit_set_wave_bins(0)
+        off_ = run()
+    finally:
+        for d, was in zip((hf._ctx, hf._pool, hf._wave_bins), contexts):
+            d.clear()
+            d.update(was)
+    for x, y in zip(first, second):
+        np.testing.assert_array_equal(x, y)
+    assert np.all((first[2] == hf.FIT_BADHIST) == (sizes == 0))
+    ok = sizes > 0
+    assert np.all(first[2][ok] == 0)
+    for k in (2, 3, 4):
+        np.testing.assert_array_equal(first[k], off_[k])
+    # both converged to EDM < 1e-10: the parameters agree to 2 sqrt(2e-10) sigma,
+    # sigma below 10% here
+    np.testing.assert_allclose(first[0][ok], off_[0][ok], rtol=3e-6, atol=3e-6)
