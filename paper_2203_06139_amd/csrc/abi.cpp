@@ -300,7 +300,7 @@ int run_objective(hf_ctx* c, const hf_hist* h, const hf_model* m, int32_t obj, i
   const int64_t items_bins =
       two_d ? ((a.nx + hf::kChunk2D - 1) / hf::kChunk2D) * hf::kChunk2D * a.ny : a.nx;
   const int chunk = two_d ? hf::kChunk2D
-                          : (avg ? hf::kAvgChunk : (edges ? 1 : hf::chunk_bins(m->n_gauss)));
+                          : (edges ? 1 : (avg ? hf::kAvgChunk : hf::chunk_bins(m->n_gauss)));
   const int grid = objective_grid(c, items_bins, chunk, per_cu, block);
   hipError_t e = fn(a, grid, stream, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "kernel launch");

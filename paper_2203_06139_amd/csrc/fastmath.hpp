@@ -21,6 +21,7 @@
 //              store ln(c_j/2) and bump e, so arguments just below 1 do not
 //              cancel against ln 2.  log_lut(0) is finite (about -709): an
 //              empty bin's n ln(n/mu) term is 0 * finite = 0.
+//   erf_from_phi  erf where exp(-z^2/2) is needed beside it.
 // Inputs must be finite; div_fast needs a positive normal divisor.
 #pragma once
 
@@ -152,6 +153,63 @@ __device__ __forceinline__ double log_lut(double x, const double2* __restrict__ 
   // 0.28 and the term it enters is large, so ~1e-16 relative is ample.
   const double ed = static_cast<double>(e);
   return fma(p, f, fma(ed, kLn2, t.y));
+}
+
+// erf(z / sqrt 2) where phi = exp(-z^2 / 2) is at hand (within a few ulp).
+// With x = |z| / sqrt 2: below 1, x times a polynomial of degree 12 in x^2;
+// from 1 on, 1 - phi erfcx(x), erfcx(x) = exp(x^2) erfc(x) as t times a
+// polynomial of degree 15 in t = 1/(x + 3), mapped to u in [-1, 1] over x =
+// 1..6 (in the manner of Shepherd & Laframboise, Math. Comp. 36, 1981, who
+// expand erfcx in (x - k)/(x + k)); beyond 6 the result is 1.  Both are
+// Chebyshev interpolants computed in 60-digit arithmetic (truncation below
+// 1e-17).  Absolute error, against 50 digits: rms 3.5e-17, at most 1.1e-16, as
+// of the library's erf, which takes about 200 instructions to these 20 to 35.
+__device__ __forceinline__ double erf_from_phi(double z, double phi) {
+  const double x = fabs(z) * 0.70710678118654752440;
+  double r;
+  // neighbouring bins mostly fall on one side, so a wave takes one branch;
+  // with both forms evaluated and selected 1e6 bins took 23.0 us, not 19.5
+  if (x < 1.0) {
+    const double w = x * x;
+    double p = 5.957176147748911e-11;
+    p = fma(p, w, -1.1372848856791674e-09);
+    p = fma(p, w, 1.4659775274047436e-08);
+    p = fma(p, w, -1.6350312701054695e-07);
+    p = fma(p, w, 1.6461000484121368e-06);
+    p = fma(p, w, -1.4925595266831182e-05);
+    p = fma(p, w, 0.0001205533111164271);
+    p = fma(p, w, -0.000854832698083379);
+    p = fma(p, w, 0.0052239776248180145);
+    p = fma(p, w, -0.026866170645076792);
+    p = fma(p, w, 0.11283791670954879);
+    p = fma(p, w, -0.3761263890318375);
+    p = fma(p, w, 1.1283791670955126);
+    r = p * x;
+  } else {
+    const double xc = x > 6.0 ? 6.0 : x;  // keeps a NaN
+    const double d = xc + 3.0;
+    double t = rcp_fast(d);
+    t = fma(t, fma(-d, t, 1.0), t);
+    const double u = fma(t, 14.4, -2.6);
+    double q = -2.279742613773115e-12;
+    q = fma(q, u, 5.830884699677111e-12);
+    q = fma(q, u, 8.098927716409088e-11);
+    q = fma(q, u, -2.9728506949500295e-10);
+    q = fma(q, u, -2.942735833696472e-09);
+    q = fma(q, u, 1.1449481840693569e-08);
+    q = fma(q, u, 1.3353032032709014e-07);
+    q = fma(q, u, -2.8199389473825003e-07);
+    q = fma(q, u, -7.246255012285937e-06);
+    q = fma(q, u, -1.608776475267465e-05);
+    q = fma(q, u, 0.00032354378790109227);
+    q = fma(q, u, 0.003933868783798848);
+    q = fma(q, u, 0.025474072799978032);
+    q = fma(q, u, 0.11683673753802074);
+    q = fma(q, u, 0.4118820962100305);
+    q = fma(q, u, 1.1519074596928367);
+    r = fma(-q * t, phi, 1.0);
+  }
+  return __builtin_copysign(r, z);
 }
 
 // S(u) = sinh(u)/u and S'(u) = (cosh u - S(u))/u: the average of

@@ -19,9 +19,10 @@
 //   1, t_c, t_c^2 + d^2/3, t_c^3 + t_c d^2   (d = h / (2 t_scale)),
 // for the exponential exp(b0 + b1 t) its exact average E_c S(b1 d) with
 // E_c = exp(b0 + b1 t_c) and S(u) = sinh(u)/u (d/db1 = E_c (t_c S + d S')).
-// A thread walks a chunk of consecutive bins edge to edge: each bin
-// evaluates erf and exp at its right edge and hands them to the next bin, so
-// a bin costs one erf and one exp per Gaussian.  On uniform bins narrower
+// Each bin evaluates erf and exp at its right edge and hands them to the next
+// bin (a thread walking uniform bins edge to edge, or a wave taking 64 bins of
+// any widths side by side), so a bin costs one erf and one exp per Gaussian.
+// On uniform bins narrower
 // than a sixteenth of every width, the Gaussians' averages and partials come
 // instead from a Hermite series about the bin centre, with exp at the
 // centres by the two-multiply recurrence (no erf; see k_nll_1d_avg).  The objective terms, the
@@ -64,17 +65,14 @@ __device__ __forceinline__ void herm_series(double z, const double (&c)[kHermMax
   }
 }
 
-// a.x0 holds the left edge of bin 0 (not its centre) for these kernels.
-// EDGES: the bins' edges come from a.x_edges (any widths), else from the
-// uniform grid.
-template <int NG, int BKG, int OBJ, bool GRAD, bool EDGES>
+// Uniform bins.  a.x0 holds the left edge of bin 0 (not its centre).
+template <int NG, int BKG, int OBJ, bool GRAD>
 __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
   using S = Shape1D<NG, BKG>;
   constexpr int P = S::P;
   constexpr int NV = GRAD ? P + 1 : 1;
   constexpr int G1 = NG > 0 ? NG : 1;
   constexpr double kRt = 1.2533141373155002512;   // sqrt(pi/2)
-  constexpr double kIr2 = 0.70710678118654752440;  // 1/sqrt(2)
   __shared__ double2 lut[OBJ == OBJ_POISSON ? kLogLut : 1];
   if constexpr (OBJ == OBJ_POISSON) log_lut_load(lut, a.log_lut);
   Model1D<NG, BKG> M;
@@ -98,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
   // sqrt n)^n) and phi < 3e-18 beyond; N = 1, 3 or 6 terms after the first
   // keep it below 1e-19, 1e-19 and 3e-18 for delta up to 4.5e-6, 1.6e-3 and
   // 1/32.
-  bool series = !EDGES && NG > 0;
+  bool series = NG > 0;
   double dmax = 0.0;
   double dzs[G1], Dz[G1], cs[G1][kHermMax + 1];
 #pragma unroll
@@ -128,12 +126,11 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
   for (int64_t c = tid; c < nch; c += stride) {
     const int64_t i0 = c * kAvgChunk;
     const int len = static_cast<int>(nb - i0 < kAvgChunk ? nb - i0 : kAvgChunk);
-    const double* __restrict__ E = EDGES ? a.x_edges : nullptr;
     // erf path: z, erf and phi at the left edge of the current bin; series
     // path: za = z at the chunk's first centre, ea = phi at the current
     // centre and Ea its ratio to the next one
     double za[G1], Ea[G1], ea[G1];
-    double xa = EDGES ? E[i0] : fma(static_cast<double>(i0), a.hx, a.x0);
+    double xa = fma(static_cast<double>(i0), a.hx, a.x0);
     if (series) {
       const double xc = fma(static_cast<double>(i0) + 0.5, a.hx, a.x0);
 #pragma unroll
@@ -147,25 +144,23 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         za[g] = (x - M.m[g]) * M.is[g];
-        Ea[g] = erf(za[g] * kIr2);
         ea[g] = exp_fast(-0.5 * za[g] * za[g]);
+        Ea[g] = erf_from_phi(za[g], ea[g]);
       }
     }
-    // the next bin's count, weight and right edge are requested while the
-    // current bin is computed (one bin's latency hidden behind its erfs)
+    // the next bin's count and weight are requested while the current bin is
+    // computed
     double n_nx = load_count1(a, i0);
     double w_nx = a.weights ? static_cast<double>(a.weights[i0]) : 1.0;
-    double xb_nx = EDGES ? E[i0 + 1] : 0.0;
     for (int k = 0; k < len; ++k) {
       const int64_t i = i0 + k;
       const double n = n_nx, w = w_nx;
-      const double xb = EDGES ? xb_nx : fma(static_cast<double>(i + 1), a.hx, a.x0);
+      const double xb = fma(static_cast<double>(i + 1), a.hx, a.x0);
       if (k + 1 < len) {
         n_nx = load_count1(a, i + 1);
         w_nx = a.weights ? static_cast<double>(a.weights[i + 1]) : 1.0;
-        if (EDGES) xb_nx = E[i + 2];
       }
-      const double ih = EDGES ? 1.0 / (xb - xa) : invh;
+      const double ih = invh;
       double mu = 0.0;
       double J[P];
       if (series) {
@@ -195,8 +190,8 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
           const double zb = (xb - M.m[g]) * M.is[g];
-          const double Eb = erf(zb * kIr2);
           const double eb = exp_fast(-0.5 * zb * zb);
+          const double Eb = erf_from_phi(zb, eb);
           const double ia = sg[g] * kRt * (Eb - Ea[g]) * ih;
           const double mg = M.A[g] * ia;
           mu += mg;
@@ -211,9 +206,9 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
         }
       }
       if constexpr (BKG == BKG_EXP) {
-        const double xc = EDGES ? 0.5 * (xa + xb) : fma(static_cast<double>(i) + 0.5, a.hx, a.x0);
+        const double xc = fma(static_cast<double>(i) + 0.5, a.hx, a.x0);
         const double tc = (xc - M.tshift) * M.ta;
-        const double dh = EDGES ? 0.5 * (xb - xa) * M.ta : d;
+        const double dh = d;
         const double Ec = exp_fast(fma(M.c[1], tc, M.c[0]));
         double Sh, dSh;
         sinhc(M.c[1] * dh, Sh, dSh);
@@ -224,9 +219,9 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
           J[3 * NG + 1] = Ec * fma(tc, Sh, dh * dSh);
         }
       } else if constexpr (S::NB > 0) {
-        const double xc = EDGES ? 0.5 * (xa + xb) : fma(static_cast<double>(i) + 0.5, a.hx, a.x0);
+        const double xc = fma(static_cast<double>(i) + 0.5, a.hx, a.x0);
         const double tc = (xc - M.tshift) * M.ta;
-        const double dh = EDGES ? 0.5 * (xb - xa) * M.ta : d;
+        const double dh = d;
         const double d2 = dh * dh;
         double avg[4];
         avg[0] = 1.0;
@@ -249,6 +244,159 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
       }
       if (a.grad_w_out) a.grad_w_out[i] = static_cast<float>(seed * l);
       xa = xb;
+    }
+  }
+  // exact partials: no final factors
+  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), nullptr, nullptr, a.part,
+                   a.part_flags);
+}
+
+// x of the lane before, `first` in lane 0.
+__device__ __forceinline__ double from_previous_lane(double x, double first) {
+  constexpr int kWaveShr1 = 0x138;
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(first), __double2loint(x), kWaveShr1, 0xf,
+                                             0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(first), __double2hiint(x), kWaveShr1, 0xf,
+                                             0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Bins of any widths.  A wave takes 64 neighbouring bins per step, each lane
+// evaluating erf and exp at its bin's right edge; the left edge's values come
+// from the lane before by a DPP move, and lane 0's from the last lane of the
+// step before (a wave's steps are consecutive; it evaluates one more edge at
+// its start).  So loads are contiguous and a bin still costs one erf and exp
+// per Gaussian.
+// Bound: VALU issue.  Two Gaussians and a line, Poisson, on the GPU with the
+// finishing kernel, against a thread walking 8 bins edge to edge with the
+// library's erf: 1003 bins 14.9 -> 7.7 us (the chain of 8 bins is gone),
+// 100,003 bins 14.9 -> 9.2, 1e6 bins 20.4 -> 19.5, 4e6 bins 61.3 -> 58.8.  Two
+// steps side by side were slower (24 us at 1e6): registers, not latency.
+template <int NG, int BKG, int OBJ, bool GRAD>
+__global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
+  using S = Shape1D<NG, BKG>;
+  constexpr int P = S::P;
+  constexpr int NV = GRAD ? P + 1 : 1;
+  constexpr int G1 = NG > 0 ? NG : 1;
+  constexpr double kRt = 1.2533141373155002512;   // sqrt(pi/2)
+  __shared__ double2 lut[OBJ == OBJ_POISSON ? kLogLut : 1];
+  if constexpr (OBJ == OBJ_POISSON) log_lut_load(lut, a.log_lut);
+  Model1D<NG, BKG> M;
+  M.init(a.theta, a.t_shift, a.t_scale);
+  double sg[G1];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) sg[g] = a.theta[3 * g + 2];
+  if constexpr (OBJ == OBJ_POISSON) __syncthreads();
+  double acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+  int flags = 0;
+  const double seed = (a.grad_w_out && a.seed) ? a.seed[0] : 1.0;  // for grad_w
+  const bool finite = all_finite(a.theta, a.P);
+  const double* __restrict__ E = a.x_edges;
+  const int64_t nb = a.nx;
+  const int64_t steps = (nb + 63) / 64;
+  const int64_t waves = static_cast<int64_t>(gridDim.x) * kWaves;
+  const int64_t wave = static_cast<int64_t>(blockIdx.x) * kWaves + (threadIdx.x >> 6);
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  const int64_t s0 = steps * wave / waves, s1 = steps * (wave + 1) / waves;
+  if (s0 < s1) {
+    // position, z, erf and phi at an edge
+    struct Edge {
+      double x, z[G1], E[G1], e[G1];
+    };
+    auto edge = [&](double x) {
+      Edge r;
+      r.x = x;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        r.z[g] = (x - M.m[g]) * M.is[g];
+        r.e[g] = exp_fast(-0.5 * r.z[g] * r.z[g]);
+        r.E[g] = erf_from_phi(r.z[g], r.e[g]);
+      }
+      return r;
+    };
+    Edge last = edge(E[64 * s0]);  // right edge of the bin before the step
+    auto bin = [&](int64_t s) {
+      const int64_t i = 64 * s + lane;
+      return i < nb ? i : nb - 1;
+    };
+    int64_t i_nx = bin(s0);
+    double x_nx = E[i_nx + 1], n_nx = load_count1(a, i_nx);
+    double w_nx = a.weights ? static_cast<double>(a.weights[i_nx]) : 1.0;
+    for (int64_t s = s0; s < s1; ++s) {
+      const int64_t i = i_nx;
+      const bool in = 64 * s + lane < nb;  // lanes past the last bin compute it again and are dropped
+      const double n = n_nx, w = w_nx;
+      const Edge right = edge(x_nx);
+      if (s + 1 < s1) {
+        i_nx = bin(s + 1);
+        x_nx = E[i_nx + 1];
+        n_nx = load_count1(a, i_nx);
+        w_nx = a.weights ? static_cast<double>(a.weights[i_nx]) : 1.0;
+      }
+      const double xa = from_previous_lane(right.x, last.x), xb = right.x;
+      const double ih = in ? 1.0 / (xb - xa) : 0.0;
+      double mu = 0.0;
+      double J[P];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const double Ea = from_previous_lane(right.E[g], last.E[g]);
+        const double ia = sg[g] * kRt * (right.E[g] - Ea) * ih;
+        const double mg = M.A[g] * ia;
+        mu += mg;
+        if constexpr (GRAD) {
+          const double za = from_previous_lane(right.z[g], last.z[g]);
+          const double ea = from_previous_lane(right.e[g], last.e[g]);
+          J[3 * g] = ia;
+          J[3 * g + 1] = M.A[g] * (ea - right.e[g]) * ih;
+          J[3 * g + 2] = fma(mg, M.is[g], M.A[g] * fma(za, ea, -right.z[g] * right.e[g]) * ih);
+        }
+      }
+      last.x = readlane_d(right.x, 63);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        last.z[g] = readlane_d(right.z[g], 63);
+        last.E[g] = readlane_d(right.E[g], 63);
+        last.e[g] = readlane_d(right.e[g], 63);
+      }
+      const double tc = (0.5 * (xa + xb) - M.tshift) * M.ta;
+      const double dh = 0.5 * (xb - xa) * M.ta;
+      if constexpr (BKG == BKG_EXP) {
+        const double Ec = exp_fast(fma(M.c[1], tc, M.c[0]));
+        double Sh, dSh;
+        sinhc(M.c[1] * dh, Sh, dSh);
+        const double eb = Ec * Sh;
+        mu += eb;
+        if constexpr (GRAD) {
+          J[3 * NG] = eb;
+          J[3 * NG + 1] = Ec * fma(tc, Sh, dh * dSh);
+        }
+      } else if constexpr (S::NB > 0) {
+        const double d2 = dh * dh;
+        double avg[4];
+        avg[0] = 1.0;
+        avg[1] = tc;
+        avg[2] = fma(tc, tc, d2 * (1.0 / 3.0));
+        avg[3] = tc * fma(tc, tc, d2);
+#pragma unroll
+        for (int j = 0; j < S::NB; ++j) {
+          mu = fma(M.c[j], avg[j], mu);
+          if constexpr (GRAD) J[3 * NG + j] = avg[j];
+        }
+      }
+      double l, ub;
+      const bool dom = objective_t<OBJ, false>(n, mu, lut, l, ub);
+      if (in) {
+        flags |= dom ? ST_DOMAIN : 0;
+        acc[0] = fma(w, l, acc[0]);
+        if constexpr (GRAD) {
+          const double mb = w * ub;
+#pragma unroll
+          for (int p = 0; p < P; ++p) acc[1 + p] = fma(mb, J[p], acc[1 + p]);
+        }
+        if (a.grad_w_out) a.grad_w_out[i] = static_cast<float>(seed * l);
+      }
     }
   }
   // exact partials: no final factors
@@ -421,8 +569,10 @@ LaunchFn pick_edges_ng(int bkg, int obj, bool grad) {
 
 template <int NG, int BKG, int OBJ, bool GRAD, bool EDGES>
 hipError_t launch_1d_avg(const NllArgs& a, int grid, hipStream_t s, int* occ, int* block) {
-  return launch_or_occupancy<kBlock>(k_nll_1d_avg<NG, BKG, OBJ, GRAD, EDGES>, a, grid, s, occ,
-                                     block);
+  if constexpr (EDGES)
+    return launch_or_occupancy<kBlock>(k_nll_1d_avg_edges<NG, BKG, OBJ, GRAD>, a, grid, s, occ, block);
+  else
+    return launch_or_occupancy<kBlock>(k_nll_1d_avg<NG, BKG, OBJ, GRAD>, a, grid, s, occ, block);
 }
 
 template <int NG, int BKG, bool EDGES>
