@@ -16,86 +16,83 @@ namespace hf {
 
 constexpr int kCovMaxP = 16;
 
+// Lane r holds row r of R and L over the free parameters, then column r of
+// inv(L), in registers, and takes the other lanes' values by readlane; rows
+// past the free ones (up to N, a multiple of 4) are the identity's.
+// Bound: the latency of one chain (N square roots and twice N divisions that
+// follow each other).  One 10 x 10 matrix: 12.0 us with the matrix in LDS and
+// a barrier per column and per pivot, 6.1 us now.
+template <int N>
 __global__ __launch_bounds__(64) void k_fisher_cov(const double* __restrict__ F, int P,
                                                    uint32_t free_mask, double scale,
                                                    double* __restrict__ cov,
                                                    int32_t* __restrict__ status) {
-  constexpr int S = kCovMaxP;
-  __shared__ double L[S * S], Li[S * S], sc[S];
-  __shared__ int fidx[S], pos[S];
-  __shared__ int nf, ok;
-  const int tid = threadIdx.x;
+  const int r = threadIdx.x;
   const int64_t b = blockIdx.x;
   const double* Fb = F + b * P * P;
   double* Cb = cov + b * P * P;
-  if (tid == 0) {
-    int k = 0;
-    for (int p = 0; p < P; ++p) {
-      const bool fr = free_mask == 0u || ((free_mask >> p) & 1u);
-      pos[p] = fr ? k : -1;
-      if (fr) fidx[k++] = p;
-    }
-    nf = k;
-    ok = 1;
+  const uint32_t all = (1u << P) - 1u;
+  const uint32_t mask = free_mask == 0u ? all : (free_mask & all);
+  const int nf = __builtin_popcount(mask);
+  // index of the r-th free parameter (this lane's) and of every one
+  int kr = 0, kc[N];
+  uint32_t left = mask;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    kc[c] = left ? __builtin_ctz(left) : 0;
+    left &= left - 1u;
+    if (c == r) kr = kc[c];
   }
-  __syncthreads();
-  if (tid < nf) {
-    const double d = Fb[fidx[tid] * P + fidx[tid]];
-    if (!(d > 0.0) || !__builtin_isfinite(d)) ok = 0;  // benign race: every writer stores 0
-    sc[tid] = 1.0 / sqrt(d);
+  const bool mine = r < nf;
+  double a[N], x[N];
+  const double d = mine ? Fb[kr * P + kr] : 1.0;
+#pragma unroll
+  for (int c = 0; c < N; ++c) a[c] = mine && c < nf ? Fb[kr * P + kc[c]] : 0.0;
+  bool ok = d > 0.0 && __builtin_isfinite(d);
+  const double sc = 1.0 / sqrt(d);
+#pragma unroll
+  for (int c = 0; c < N; ++c)
+    a[c] = mine && c < nf ? a[c] * sc * readlane_d(sc, c) : (r == c ? 1.0 : 0.0);
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    const double p = readlane_d(a[j], j);
+    if (!(p > 1e-12) || !__builtin_isfinite(p)) ok = false;  // 1 past the free rows
+    const double piv = sqrt(p);
+    a[j] = r == j ? piv : a[j] / piv;
+#pragma unroll
+    for (int c = j + 1; c < N; ++c) a[c] = fma(-a[j], readlane_d(a[j], c), a[c]);
   }
-  __syncthreads();
-  for (int t = tid; t < nf * nf; t += 64) {
-    const int r = t / nf, c = t % nf;
-    L[r * S + c] = ok ? Fb[fidx[r] * P + fidx[c]] * sc[r] * sc[c] : 0.0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    double v = r == i ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < i; ++k) v = fma(-readlane_d(a[k], i), x[k], v);
+    x[i] = v / readlane_d(a[i], i);
   }
-  __syncthreads();
-  for (int j = 0; j < nf && ok; ++j) {
-    if (tid == 0) {
-      double d = L[j * S + j];
-      for (int k = 0; k < j; ++k) d -= L[j * S + k] * L[j * S + k];
-      if (!(d > 1e-12) || !__builtin_isfinite(d)) ok = 0;
-      else L[j * S + j] = sqrt(d);
-    }
-    __syncthreads();
-    if (ok && tid > j && tid < nf) {
-      double v = L[tid * S + j];
-      for (int k = 0; k < j; ++k) v -= L[tid * S + k] * L[j * S + k];
-      L[tid * S + j] = v / L[j * S + j];
-    }
-    __syncthreads();
-  }
-  if (ok && tid < nf) {  // column tid of inv(L)
-    const int c = tid;
-    for (int i = c; i < nf; ++i) {
-      double v = (i == c) ? 1.0 : 0.0;
-      for (int k = c; k < i; ++k) v -= L[i * S + k] * Li[k * S + c];
-      Li[i * S + c] = v / L[i * S + i];
-    }
-  }
-  __syncthreads();
-  const double nan = __builtin_nan("");
-  for (int t = tid; t < P * P; t += 64) {
-    const int pr = pos[t / P], pc = pos[t % P];
+  ok = __all(ok);
+  // rows and columns of fixed parameters
+  for (int t = r; t < P * P; t += 64)
+    if (!((mask >> (t / P)) & (mask >> (t % P)) & 1u)) Cb[t] = 0.0;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
     double v = 0.0;
-    if (pr >= 0 && pc >= 0) {
-      if (ok) {
-        for (int k = (pr > pc ? pr : pc); k < nf; ++k) v += Li[k * S + pr] * Li[k * S + pc];
-        v *= scale * sc[pr] * sc[pc];
-      } else {
-        v = nan;
-      }
-    }
-    Cb[t] = v;
+#pragma unroll
+    for (int k = c; k < N; ++k) v = fma(x[k], readlane_d(x[k], c), v);
+    v *= scale * sc * readlane_d(sc, c);
+    if (mine && c < nf) Cb[kr * P + kc[c]] = ok ? v : __builtin_nan("");
   }
-  if (tid == 0 && status) status[b] = ok ? 0 : 1;
+  if (r == 0 && status) status[b] = ok ? 0 : 1;
 }
 
 hipError_t fisher_covariance(int B, int P, const double* F, uint32_t free_mask, double scale,
                              double* cov, int32_t* status, hipStream_t s) {
   if (B <= 0) return hipSuccess;
   if (P < 1 || P > kCovMaxP) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_fisher_cov, dim3(B), dim3(64), 0, s, F, P, free_mask, scale, cov, status);
+  const uint32_t all = (1u << P) - 1u;
+  const int nf = __builtin_popcount(free_mask == 0u ? all : (free_mask & all));
+  const auto k = nf <= 4 ? k_fisher_cov<4>
+                         : (nf <= 8 ? k_fisher_cov<8> : (nf <= 12 ? k_fisher_cov<12> : k_fisher_cov<16>));
+  hipLaunchKernelGGL(k, dim3(B), dim3(64), 0, s, F, P, free_mask, scale, cov, status);
   return hipGetLastError();
 }
 
