@@ -304,6 +304,7 @@ int run_objective(hf_ctx* c, const hf_hist* h, const hf_model* m, int32_t obj, i
   const int grid = objective_grid(c, items_bins, chunk, per_cu, block);
   hipError_t e = fn(a, grid, stream, nullptr, nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "kernel launch");
+  if (grid == 1) return HF_OK;  // a single block writes the outputs itself
   hf::FinishArgs f{};
   f.part = c->part;
   f.part_flags = c->part_flags;
@@ -548,6 +549,7 @@ HF_EXPORT int nll_unbinned(hf_ctx* c, const double* events, const float* weights
   const int cap = c->blocks_per_cu > 0 ? std::min(kMaxGrid, c->num_cu * c->blocks_per_cu) : kMaxGrid;
   hipError_t e = fn(a, vec, c->num_cu, cap, reinterpret_cast<hipStream_t>(stream), &grid);
   if (e != hipSuccess) return hip_fail(c, e, "kernel launch");
+  if (grid == 1) return HF_OK;  // a single block writes the outputs itself
   hf::FinishArgs f{};
   f.part = c->part;
   f.part_flags = c->part_flags;
@@ -632,6 +634,7 @@ HF_EXPORT int hf_nll_fisher(hf_ctx* c, const hf_hist* h, const hf_model* m, int3
   for (int p = 0; p < passes; ++p) {
     hipError_t e = fn(a, p, grid, stream, nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "kernel launch");
+    if (grid == 1) continue;  // a single block writes its entries itself
     hf::FinishSymArgs f{};
     f.part = c->part;
     f.part_flags = c->part_flags;

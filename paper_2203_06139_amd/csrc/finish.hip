@@ -58,18 +58,8 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_split(FinishArgs a) {
     }
   }
   block_sum<1, WAVES>(v, f, tot, &totf, red, redf);
-  if (threadIdx.x == 0) {
-    const double nan = __builtin_nan("");
-    const bool finite = (totf & ST_NONFINITE) == 0;
-    const bool domain = (totf & ST_DOMAIN) != 0;
-    if (k == 0) {
-      a.nll_out[0] = !finite ? nan : (domain ? __builtin_inf() : tot[0]);
-      if (a.status_out) a.status_out[0] = totf;
-    } else {
-      const bool free = (a.free_mask == 0u) || ((a.free_mask >> (k - 1)) & 1u);
-      a.grad_out[k - 1] = (!finite || domain) ? nan : (free ? tot[0] * seed : 0.0);
-    }
-  }
+  if (threadIdx.x == 0)
+    write_output({a.nll_out, a.grad_out, a.status_out, a.free_mask}, k, tot[0], totf, seed);
 }
 
 // One block per entry: the block's threads take the G partials in a fixed
@@ -104,19 +94,7 @@ __global__ __launch_bounds__(kFinishBlock) void k_finish_sym(FinishSymArgs a) {
     }
   }
   block_sum<1, WAVES>(v, f, tot, &totf, red, redf);
-  if (threadIdx.x == 0) {
-    int r = 0, e = a.E0 + q;
-    while (e >= a.P - r) {
-      e -= a.P - r;
-      ++r;
-    }
-    const int c = r + e;
-    const bool finite = (totf & ST_NONFINITE) == 0;
-    const double val = finite ? tot[0] : __builtin_nan("");
-    a.out[r * a.P + c] = val;
-    a.out[c * a.P + r] = val;
-    if (q == 0 && a.E0 == 0 && a.status_out) a.status_out[0] = finite ? 0 : ST_NONFINITE;
-  }
+  if (threadIdx.x == 0) write_entry({a.out, a.status_out, a.P, a.E0}, q, tot[0], totf);
 }
 
 }  // namespace

@@ -540,7 +540,10 @@ __device__ __forceinline__ void fisher_publish(const FisherArgs& a, const M& mod
     fac[q] = ff[r] * ff[r + e] * a.cfac;
   }
   // (block_sum's barriers inside grid_publish order these writes before use)
-  grid_publish<NQ>(acc, finite ? 0 : ST_NONFINITE, fac, nullptr, a.part, a.part_flags);
+  grid_publish<NQ>(acc, finite ? 0 : ST_NONFINITE, fac, nullptr, a.part, a.part_flags,
+                   [&](int k, double x, int f) {
+                     write_entry({a.fisher_out, a.status_out, P, E0}, k, x, f);
+                   });
 }
 
 template <int NG, int BKG, bool NEY, int PASS>

@@ -196,17 +196,13 @@ __device__ __forceinline__ void gsync() {
 
 // Each wave's sums of v and its flags into red and redf.
 template <int NV, int BLK>
-__device__ __forceinline__ void wave_totals(double (&v)[NV], int flags, double (*red)[NV], int* redf) {
-#pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = wave_sum(v[k]);
+__device__ __forceinline__ void wave_totals(const double (&v)[NV], int flags, double (*red)[NV],
+                                            int* redf) {
+  const int wid = BLK == 64 ? 0 : static_cast<int>(threadIdx.x >> 6);
+  wave_sums(v, [&](int k, double x) { red[wid][k] = x; });
   const int f = (__ballot(flags & ST_DOMAIN) ? ST_DOMAIN : 0) |
                 (__ballot(flags & ST_NONFINITE) ? ST_NONFINITE : 0);
-  const int wid = BLK == 64 ? 0 : static_cast<int>(threadIdx.x >> 6);
-  if ((threadIdx.x & 63u) == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) red[wid][k] = v[k];
-    redf[wid] = f;
-  }
+  if ((threadIdx.x & 63u) == 0) redf[wid] = f;
 }
 
 // The group's total of component k, the waves added in order.

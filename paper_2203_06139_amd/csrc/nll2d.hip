@@ -200,8 +200,7 @@ __global__ __launch_bounds__(kBlock, kMinWaves) void k_nll_2d(NllArgs a) {
 
   __shared__ double fac[NV];
   if (threadIdx.x < NV) fac[threadIdx.x] = M.final_factor(threadIdx.x);
-  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), fac, nullptr, a.part,
-                   a.part_flags);
+  publish_objective<NV>(a, acc, flags | (finite ? 0 : ST_NONFINITE), fac, output_seed(a));
 }
 
 template <int OBJ, bool GRAD, bool F32BIN>

@@ -247,8 +247,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
     }
   }
   // exact partials: no final factors
-  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), nullptr, nullptr, a.part,
-                   a.part_flags);
+  publish_objective<NV>(a, acc, flags | (finite ? 0 : ST_NONFINITE), nullptr, output_seed(a));
 }
 
 // x of the lane before, `first` in lane 0.
@@ -400,8 +399,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
     }
   }
   // exact partials: no final factors
-  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), nullptr, nullptr, a.part,
-                   a.part_flags);
+  publish_objective<NV>(a, acc, flags | (finite ? 0 : ST_NONFINITE), nullptr, output_seed(a));
 }
 
 // Centre model on bins of any widths: mu at each bin's midpoint, with the
@@ -520,8 +518,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_edges(NllArgs a) {
   }
   __shared__ double fac[NV];
   if (threadIdx.x < NV) fac[threadIdx.x] = M.final_factor(threadIdx.x);
-  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), fac, nullptr, a.part,
-                   a.part_flags);
+  publish_objective<NV>(a, acc, flags | (finite ? 0 : ST_NONFINITE), fac, output_seed(a));
 }
 
 template <int NG, int BKG, int OBJ, bool GRAD>

@@ -39,11 +39,28 @@ struct NllArgs {
   const double* x_edges;   // 1D bins of any widths: nx + 1 ascending edges, or null
 };
 
+// The upstream adjoint a single-block call applies itself (read with the
+// other inputs, so that its latency is not paid at the end).
+__device__ __forceinline__ double output_seed(const NllArgs& a) {
+  return gridDim.x == 1 && a.seed ? a.seed[0] : 1.0;
+}
+
+// grid_publish for the objective kernels: a single block writes the outputs.
+template <int NV, int BLOCK = kBlock>
+__device__ __forceinline__ void publish_objective(const NllArgs& a, const double (&acc)[NV], int flags,
+                                                  const double* fac, double out_seed) {
+  grid_publish<NV, BLOCK>(acc, flags, fac, nullptr, a.part, a.part_flags,
+                          [&](int k, double x, int f) {
+                            write_output({a.nll_out, a.grad_out, a.status_out, a.free_mask}, k, x, f,
+                                         out_seed);
+                          });
+}
+
 // Launches a kernel variant with `grid` blocks; grid <= 0 instead returns,
 // through *occ, how many blocks of that kernel fit on one CU at once, and
 // through *block its threads per block.  The main kernel only publishes
 // per-block partials (grid_publish); the caller launches the finishing
-// kernel (launch_finish) after it.
+// kernel (launch_finish) after a grid of more than one block.
 using LaunchFn = hipError_t (*)(const NllArgs&, int grid, hipStream_t, int* occ, int* block);
 
 __device__ __forceinline__ void load_counts4(const NllArgs& a, int64_t i0, double (&n)[4]) {
@@ -218,9 +235,10 @@ __global__ __launch_bounds__((Chunking<NG, OBJ>::BLOCK), (Chunking<NG, OBJ>::W))
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;
   int flags = 0;
-  // the upstream adjoint scales grad_w here; the finishing kernel applies it
-  // to the parameter gradient
+  // the upstream adjoint scales grad_w here; the finishing kernel (or a single
+  // block) applies it to the parameter gradient
   const double seed = (a.grad_w_out && a.seed) ? a.seed[0] : 1.0;
+  const double out_seed = output_seed(a);
   const bool finite = all_finite(a.theta, a.P);
 
   if (spec) {
@@ -255,8 +273,7 @@ __global__ __launch_bounds__((Chunking<NG, OBJ>::BLOCK), (Chunking<NG, OBJ>::W))
 
   __shared__ double fac[NV];
   if (threadIdx.x < NV) fac[threadIdx.x] = M.final_factor(threadIdx.x);
-  grid_publish<NV, BLOCK>(acc, flags | (finite ? 0 : ST_NONFINITE), fac, nullptr, a.part,
-                          a.part_flags);
+  publish_objective<NV, BLOCK>(a, acc, flags | (finite ? 0 : ST_NONFINITE), fac, out_seed);
 }
 
 template <int BLOCK, class K>

@@ -44,7 +44,8 @@ struct UnbinnedArgs {
 };
 
 // Launches the main kernel and returns the grid it used through *grid_used
-// (the caller then launches the finishing kernel over that many partials).
+// (the caller then launches the finishing kernel over that many partials,
+// unless one block has written the outputs itself).
 using UnbinnedFn = hipError_t (*)(const UnbinnedArgs&, bool vec, int num_cu, int max_grid,
                                   hipStream_t, int* grid_used);
 
@@ -229,7 +230,10 @@ __global__ __launch_bounds__(kBlock) void k_nll_unbinned(UnbinnedArgs a) {
   // the final factors, and block 0 adds Lambda and its derivatives
   __shared__ double fac[NV];
   if (threadIdx.x < NV) fac[threadIdx.x] = -ff[threadIdx.x];
-  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), fac, lamd, a.part, a.part_flags);
+  grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), fac, lamd, a.part, a.part_flags,
+                   [&](int k, double x, int f) {
+                     write_output({a.nll_out, a.grad_out, a.status_out, 0u}, k, x, f, 1.0);
+                   });
 }
 
 // Blocks per CU that fit (queried once per variant) bound a single round.
