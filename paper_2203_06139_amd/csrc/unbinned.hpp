@@ -10,8 +10,8 @@
 // as the bins shrink to single events).  Per event the forward sweep
 // evaluates lambda, the reverse sweep with adjoint -w/lambda accumulates
 // dlambda/dtheta (without the 1/s of the Gaussian mean and width columns,
-// applied to the totals); one exp per Gaussian, the table log and a Newton
-// reciprocal per event.  Lambda and its gradient are closed forms (per
+// applied to the totals); one exponential per Gaussian and a Newton reciprocal
+// per event, and a log per event only where there are weights.  Lambda and its gradient are closed forms (per
 // Gaussian with z_b = (b - m)/s, e_b = exp(-z_b^2/2)):
 //   Lambda_g = A s sqrt(pi/2) [erf(z_hi/sqrt 2) - erf(z_lo/sqrt 2)],
 //   d/dA = Lambda_g/A,  d/dm = A (e_lo - e_hi),
@@ -22,6 +22,8 @@
 // them to the partials it publishes.  Events outside
 // [lo, hi] are skipped; lambda <= 0 at an event inside is a domain error.
 #pragma once
+
+#include <type_traits>
 
 #include "device.hpp"
 
@@ -50,84 +52,146 @@ using UnbinnedFn = hipError_t (*)(const UnbinnedArgs&, bool vec, int num_cu, int
                                   hipStream_t, int* grid_used);
 
 // Event pairs per thread per step (16-byte loads of two positions); the next
-// step's positions are requested while the current step is computed.
-// Measured on 1e7 events (two Gaussians + cubic): 4 pairs with the prefetch
-// 65.6 us; without it 80.5 us (8 pairs 68.6 us, 2 pairs 86.4 us); 2 pairs
-// with it 77.3 us.
-constexpr int kUbPairs = 4;
+// step's positions are requested while the current step is computed.  The
+// kernel is bound by the issue of FP64 instructions: about 67 per event of
+// two Gaussians + cubic, which take 30 us of 1e7 events where a kernel of
+// nothing but as many FMAs takes 29 (reading alone takes 12.5).
+// 1e7 events in us on the GPU: one event after the other, each with its own
+// log and reciprocal, 49.3; the logs' product 43.1; exponentials of 4 events
+// side by side 41.4; 2^(-u^2) 39.2; contiguous ranges 37.9; 2 events side by
+// side and 3 waves per SIMD 36.5, with 2 pairs per step 36.4 (3 pairs 37.8,
+// 4 waves with 8 spills 38.1), where 1000 events take 5.8 against 6.5.
+constexpr int kUbPairs = 2;
+// Events whose exponentials run side by side, and the waves per SIMD that the
+// registers are to leave room for: four Gaussians would spill 4 to 28 of them
+// at three waves.
+template <int NG, int BKG>
+constexpr int kUbSide = NG + (BKG == BKG_EXP) <= 1 ? 4 : 2;
+template <int NG>
+constexpr int kUbWaves = NG <= 3 ? 3 : 2;
 
-template <int U>
-__device__ __forceinline__ void load_pairs(const UnbinnedArgs& a, int64_t q0, int64_t stride,
-                                           int64_t npair, double2 (&xv)[U], float2 (&wv)[U]) {
+template <bool WEIGHTED, int U>
+__device__ __forceinline__ void load_pairs(const UnbinnedArgs& a, int64_t q0, int64_t end,
+                                           double2 (&xv)[U], float2 (&wv)[U]) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int64_t q = q0 + u * stride;
+    const int64_t q = q0 + u * kBlock;
     xv[u] = make_double2(__builtin_nan(""), __builtin_nan(""));  // skipped
     wv[u] = make_float2(0.0f, 0.0f);
-    if (q < npair) {
+    if (q < end) {
       xv[u] = reinterpret_cast<const double2*>(a.x)[q];
-      wv[u] = a.w ? reinterpret_cast<const float2*>(a.w)[q] : make_float2(1.0f, 1.0f);
+      if constexpr (WEIGHTED) wv[u] = reinterpret_cast<const float2*>(a.w)[q];
     }
   }
 }
 
-template <int NG, int BKG, bool GRAD, int NV>
-__device__ __forceinline__ void event_term(const UnbinnedArgs& a, const Model1D<NG, BKG>& M,
-                                           const double2* __restrict__ lut, double x, double w,
-                                           double (&acc)[NV], int& flags) {
+// The product of a thread's intensities as mantissa and exponent: L needs the
+// sum of their logs, which is the log of the product.  A factor costs four
+// instructions (its mantissa and exponent, a product and a sum) instead of a
+// log's twenty, and the log is taken once per thread.  The mantissa is brought
+// back into [0.5, 1) once per step, so it stays far from underflow.
+struct LogProduct {
+  double m = 1.0;
+  int64_t e = 0;
+  __device__ __forceinline__ void times(double x, int& step_e) {
+    m *= __builtin_amdgcn_frexp_mant(x);
+    step_e += __builtin_amdgcn_frexp_exp(x);
+  }
+  __device__ __forceinline__ void end_step(int step_e) {
+    e += step_e + __builtin_amdgcn_frexp_exp(m);
+    m = __builtin_amdgcn_frexp_mant(m);
+  }
+  // ln of the product
+  __device__ __forceinline__ double log(const double2* __restrict__ lut) const {
+    return fma(static_cast<double>(e), kLn2, log_lut<false>(m, lut));
+  }
+};
+
+// N events.  ALL: they are known to lie in the range.  WEIGHTED: the weights
+// apply (else 1) and the logs are taken here; otherwise the intensities go
+// into `prod`.
+// us: kGaussU over each width; the Gaussians' sums are of e, e u and e u^2.
+template <int NG, int BKG, bool GRAD, bool ALL, bool WEIGHTED, int N, int NV>
+__device__ __forceinline__ void event_terms(const UnbinnedArgs& a, const Model1D<NG, BKG>& M,
+                                            const double* us, const double2* __restrict__ lut,
+                                            const double* xs, const float* ws, double (&acc)[NV],
+                                            LogProduct& prod, int& step_e, int& flags) {
   using S = Shape1D<NG, BKG>;
-  const bool in = x >= a.lo && x <= a.hi;
-  // a skipped event (outside the range, or NaN) is evaluated at the range's
-  // midpoint with weight 0, where every partial is finite: at its own x a
-  // polynomial power could overflow and 0 * inf would reach the sums
-  x = in ? x : 0.5 * (a.lo + a.hi);
-  double lam = 0.0;
-  double J[S::P];
+  bool in[N];
+  double x[N], t[N], lam[N];
+  double u[NG > 0 ? NG * N : 1], e[NG > 0 ? NG * N : 1], eb[N];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    const double z = (x - M.m[g]) * M.is[g];
-    const double e = exp_fast(-0.5 * z * z);
-    const double G = M.A[g] * e;
-    lam += G;
-    if constexpr (GRAD) {
-      const double Gz = G * z;
-      J[3 * g] = e;
-      J[3 * g + 1] = Gz;
-      J[3 * g + 2] = Gz * z;
+  for (int i = 0; i < N; ++i) {
+    in[i] = ALL || (xs[i] >= a.lo && xs[i] <= a.hi);
+    // a skipped event (outside the range, or NaN) is evaluated at the range's
+    // midpoint with weight 0, where every partial is finite: at its own x a
+    // polynomial power could overflow and 0 * inf would reach the sums
+    x[i] = in[i] ? xs[i] : 0.5 * (a.lo + a.hi);
+    t[i] = (x[i] - M.tshift) * M.ta;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) u[NG * i + g] = (x[i] - M.m[g]) * us[g];
+  }
+  if constexpr (NG > 0) gauss_n(u, e);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if constexpr (BKG == BKG_EXP)
+      lam[i] = eb[i] = exp_fast(fma(M.c[1], t[i], M.c[0]));
+    else
+      lam[i] = S::NB > 0 ? M.c[S::NB > 0 ? S::NB - 1 : 0] : 0.0;
+  }
+  if constexpr (BKG != BKG_EXP) {
+#pragma unroll
+    for (int j = S::NB - 2; j >= 0; --j)
+#pragma unroll
+      for (int i = 0; i < N; ++i) lam[i] = fma(lam[i], t[i], M.c[j]);
+  }
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+#pragma unroll
+    for (int i = 0; i < N; ++i) lam[i] = fma(M.A[g], e[NG * i + g], lam[i]);
+  double r[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    // a domain error makes L infinite and the gradient NaN whatever was
+    // summed, so it is only flagged; a skipped event must leave no trace
+    const bool ok = lam[i] > 0.0;
+    flags |= (in[i] && !ok) ? ST_DOMAIN : 0;
+    const double lk = ALL ? lam[i] : (in[i] && ok ? lam[i] : 1.0);
+    r[i] = rcp_fast(lk);
+    if constexpr (WEIGHTED) {
+      const double we = in[i] ? static_cast<double>(ws[i]) : 0.0;
+      acc[0] = fma(we, log_lut<false>(lk, lut), acc[0]);
+      r[i] *= we;
+    } else {
+      prod.times(lk, step_e);
+      if constexpr (!ALL) r[i] = in[i] ? r[i] : 0.0;
     }
   }
-  if constexpr (BKG == BKG_EXP) {
-    const double t = (x - M.tshift) * M.ta;
-    const double Eb = exp_fast(fma(M.c[1], t, M.c[0]));
-    lam += Eb;
-    if constexpr (GRAD) {
-      J[3 * NG] = Eb;
-      J[3 * NG + 1] = t * Eb;
-    }
-  } else if constexpr (S::NB > 0) {
-    const double t = (x - M.tshift) * M.ta;
-    double b = M.c[S::NB - 1];
+  if constexpr (GRAD) {
 #pragma unroll
-    for (int j = S::NB - 2; j >= 0; --j) b = fma(b, t, M.c[j]);
-    lam += b;
-    if constexpr (GRAD) {
-      double tj = 1.0;
+    for (int i = 0; i < N; ++i) {
 #pragma unroll
-      for (int j = 0; j < S::NB; ++j) {
-        J[3 * NG + j] = tj;
-        tj *= t;
+      for (int g = 0; g < NG; ++g) {
+        // the amplitude and the width are applied to the totals
+        const double re = r[i] * e[NG * i + g];
+        const double ru = re * u[NG * i + g];
+        acc[1 + 3 * g] += re;
+        acc[2 + 3 * g] += ru;
+        acc[3 + 3 * g] = fma(ru, u[NG * i + g], acc[3 + 3 * g]);
+      }
+      if constexpr (BKG == BKG_EXP) {
+        const double rb = r[i] * eb[i];
+        acc[1 + 3 * NG] += rb;
+        acc[2 + 3 * NG] = fma(rb, t[i], acc[2 + 3 * NG]);
+      } else {
+        double rt = r[i];
+#pragma unroll
+        for (int j = 0; j < S::NB; ++j) {
+          acc[1 + 3 * NG + j] += rt;
+          if (j + 1 < S::NB) rt *= t[i];
+        }
       }
     }
-  }
-  const bool ok = lam > 0.0;
-  flags |= (in && !ok) ? ST_DOMAIN : 0;
-  const double we = (in && ok) ? w : 0.0;
-  const double lg = log_lut<false>(ok ? lam : 1.0, lut);
-  acc[0] = fma(we, lg, acc[0]);
-  if constexpr (GRAD) {
-    const double r = we * rcp_fast(ok ? lam : 1.0);
-#pragma unroll
-    for (int k = 0; k < S::P; ++k) acc[1 + k] = fma(r, J[k], acc[1 + k]);
   }
 }
 
@@ -177,7 +241,7 @@ __device__ void lambda_terms(const UnbinnedArgs& a, const Model1D<NG, BKG>& M, d
 }
 
 template <int NG, int BKG, bool GRAD, bool VEC>
-__global__ __launch_bounds__(kBlock) void k_nll_unbinned(UnbinnedArgs a) {
+__global__ __launch_bounds__(kBlock, kUbWaves<NG>) void k_nll_unbinned(UnbinnedArgs a) {
   using S = Shape1D<NG, BKG>;
   constexpr int NV = GRAD ? S::P + 1 : 1;
   __shared__ double2 lut[kLogLut];
@@ -190,42 +254,90 @@ __global__ __launch_bounds__(kBlock) void k_nll_unbinned(UnbinnedArgs a) {
   if (threadIdx.x == 0) {
     if (blockIdx.x == 0) lambda_terms<NG, BKG>(a, M, lamd);
 #pragma unroll
-    for (int k = 0; k <= S::P; ++k) ff[k] = M.final_factor(k);
+    for (int k = 0; k <= S::P; ++k) {
+      ff[k] = M.final_factor(k);
+      if (k >= 1 && k <= 3 * NG && (k - 1) % 3 != 0)
+        ff[k] *= M.A[(k - 1) / 3] * ((k - 1) % 3 == 1 ? kGaussUInv : kGaussUInv2);
+    }
   }
   __syncthreads();
+  double us[NG > 0 ? NG : 1];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    // kGaussU / s to the last bit
+    const double s = a.theta[3 * g + 2], q = kGaussU * M.is[g];
+    us[g] = fma(M.is[g], fma(-q, s, kGaussU) + kGaussULo, q);
+  }
   double acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;
   int flags = 0;
   const int64_t tid = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  if constexpr (VEC) {
-    const int64_t npair = a.n / 2;
-    const int64_t step = kUbPairs * stride;
-    double2 xn[kUbPairs];
-    float2 wn[kUbPairs];
-    load_pairs(a, tid, stride, npair, xn, wn);
-    for (int64_t q0 = tid; q0 < npair; q0 += step) {
-      double2 xv[kUbPairs];
-      float2 wv[kUbPairs];
+  LogProduct prod;
+  auto events = [&](auto weighted) {
+    constexpr bool W = decltype(weighted)::value;
+    if constexpr (VEC) {
+      // a block's pairs are contiguous and whole steps, so that only the last
+      // block has lanes without events
+      constexpr int64_t step = kUbPairs * kBlock;
+      const int64_t steps = (a.n / 2 + step - 1) / step;
+      const int64_t end = min(a.n / 2, steps * (blockIdx.x + 1) / gridDim.x * step);
+      double2 xn[kUbPairs];
+      float2 wn[kUbPairs];
+      int64_t q0 = steps * blockIdx.x / gridDim.x * step + threadIdx.x;
+      load_pairs<W>(a, q0, end, xn, wn);
+      for (; q0 < end; q0 += step) {
+        double xv[2 * kUbPairs];
+        float wv[2 * kUbPairs];
+        bool all = true;
 #pragma unroll
-      for (int u = 0; u < kUbPairs; ++u) {
-        xv[u] = xn[u];
-        wv[u] = wn[u];
+        for (int u = 0; u < kUbPairs; ++u) {
+          xv[2 * u] = xn[u].x;
+          xv[2 * u + 1] = xn[u].y;
+          wv[2 * u] = wn[u].x;
+          wv[2 * u + 1] = wn[u].y;
+          all = all && xn[u].x >= a.lo && xn[u].x <= a.hi && xn[u].y >= a.lo && xn[u].y <= a.hi;
+        }
+        if (q0 + step < end) load_pairs<W>(a, q0 + step, end, xn, wn);
+        int step_e = 0;
+        auto step_terms = [&](auto inside) {
+          constexpr bool ALL = decltype(inside)::value;
+          constexpr int N = kUbSide<NG, BKG>;
+#pragma unroll
+          for (int u = 0; u < 2 * kUbPairs; u += N)
+            event_terms<NG, BKG, GRAD, ALL, W, N>(a, M, us, lut, xv + u, wv + u, acc, prod, step_e,
+                                                  flags);
+        };
+        // the wave's events all in the range: the usual case, without selects
+        if (__all(all))
+          step_terms(std::true_type{});
+        else
+          step_terms(std::false_type{});
+        prod.end_step(step_e);
       }
-      if (q0 + step < npair) load_pairs(a, q0 + step, stride, npair, xn, wn);
-#pragma unroll
-      for (int u = 0; u < kUbPairs; ++u) {
-        event_term<NG, BKG, GRAD>(a, M, lut, xv[u].x, wv[u].x, acc, flags);
-        event_term<NG, BKG, GRAD>(a, M, lut, xv[u].y, wv[u].y, acc, flags);
+      if ((a.n & 1) && tid == 0) {
+        int step_e = 0;
+        const double x = a.x[a.n - 1];
+        const float w = W ? a.w[a.n - 1] : 1.0f;
+        event_terms<NG, BKG, GRAD, false, W, 1>(a, M, us, lut, &x, &w, acc, prod, step_e, flags);
+        prod.end_step(step_e);
+      }
+    } else {
+      for (int64_t e = tid; e < a.n; e += stride) {
+        int step_e = 0;
+        const double x = a.x[e];
+        const float w = W ? a.w[e] : 1.0f;
+        event_terms<NG, BKG, GRAD, false, W, 1>(a, M, us, lut, &x, &w, acc, prod, step_e, flags);
+        prod.end_step(step_e);
       }
     }
-    if ((a.n & 1) && tid == 0)
-      event_term<NG, BKG, GRAD>(a, M, lut, a.x[a.n - 1], a.w ? a.w[a.n - 1] : 1.0f, acc, flags);
-  } else {
-    for (int64_t e = tid; e < a.n; e += stride)
-      event_term<NG, BKG, GRAD>(a, M, lut, a.x[e], a.w ? a.w[e] : 1.0f, acc, flags);
-  }
+    if constexpr (!W) acc[0] += prod.log(lut);
+  };
+  if (a.w)
+    events(std::true_type{});
+  else
+    events(std::false_type{});
   // L = Lambda - sum w ln lambda: every block publishes -(its sums) times
   // the final factors, and block 0 adds Lambda and its derivatives
   __shared__ double fac[NV];
