@@ -4,6 +4,9 @@ The binding only marshals arguments: torch tensors supply device memory and
 the current HIP stream, and every step of the computation runs in the HIP
 kernels behind the C ABI declared in include/histfit.h.  There is no CPU
 fallback: if the library is missing or no GPU is visible, the calls raise.
+Calls whose arguments already are what the kernels need are marshalled
+natively (binding/fastcall.cpp); the Python code below them converts, checks
+and raises in every other case.
 
 Calls (same names as the C ABI):
   nll_eval(hist, model, theta, objective=POISSON, precision=FP64)
@@ -89,6 +92,7 @@ class HistfitError(RuntimeError):
 
 
 _lib = None
+_fast = None   # the native marshalling module, once loaded
 _ctx = {}      # (device, stream handle) -> hf_ctx
 _pool = {}     # device -> contexts created ahead, not yet given to a stream
 _tuning = {}   # device -> (wg_per_cu, cache_bins, block_size) set by fit_set_tuning
@@ -97,13 +101,18 @@ POOL_SIZE = 4  # spare contexts kept for streams first seen during graph capture
 
 
 def load():
-    """Load libhistfit.so (after torch, so both share one HIP runtime)."""
-    global _lib
+    """Load libhistfit.so (after torch, so both share one HIP runtime) and the
+    native marshalling module."""
+    global _lib, _fast
     if _lib is not None:
         return _lib
     import torch  # noqa: F401  -- binds libamdhip64 before our library
     if not os.path.exists(LIB_PATH):
         raise HistfitError("libhistfit.so is not built (run __graft_entry__.build())")
+    try:
+        from . import _fastcall
+    except ImportError as e:
+        raise HistfitError("_fastcall.so is not built (run __graft_entry__.build()): %s" % e)
     L = ctypes.CDLL(LIB_PATH)
     vp, i32, u32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint32, ctypes.c_int64
     L.hf_ctx_create.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_int]
@@ -158,6 +167,8 @@ def load():
                L.hf_fit_get_tuning, L.hf_fit_max_cache_bins, L.hf_fit_set_wave_bins,
                L.hf_fit_get_wave_bins, L.hf_fit_max_wave_bins):
         fn.restype = ctypes.c_int
+    _fastcall.init(L._handle)
+    _fast = _fastcall
     _lib = L
     return L
 
@@ -187,7 +198,10 @@ def context(device: int | None = None, stream=None):
     which a stream being captured into a graph must not do, so calls outside
     capture keep POOL_SIZE spare contexts ready, and a stream first seen
     during capture takes one of them.  `stream` defaults to the device's
-    current torch stream."""
+    current torch stream.  A context is entered into the native marshalling
+    module while the spare contexts are complete; the native calls do not come
+    through here, so they are all taken out again when a capture takes a spare
+    one, and the next call outside capture makes it up."""
     import torch
     load()
     if not torch.cuda.is_available():
@@ -199,6 +213,7 @@ def context(device: int | None = None, stream=None):
     h = _ctx.get(key)
     pool = _pool.setdefault(dev, [])
     if h is not None and len(pool) >= POOL_SIZE:
+        _fast.enter(dev, key[1], h.value)
         return h
     capturing = torch.cuda.is_current_stream_capturing()
     if h is None:
@@ -212,6 +227,9 @@ def context(device: int | None = None, stream=None):
     if not capturing:
         while len(pool) < POOL_SIZE:
             pool.append(_new_context(dev))
+        _fast.enter(dev, key[1], h.value)
+    else:
+        _fast.leave(dev)
     return h
 
 
@@ -361,6 +379,10 @@ def _check_hist_sizes(hist: Hist):
 def nll_eval(hist: Hist, model: Model, theta, objective=POISSON, precision=FP64, out=None,
              status=None):
     """L(theta) as a device f64[1] tensor (and the status word if asked for)."""
+    if _fast is not None:
+        r = _fast.nll_eval(hist, model, theta, objective, precision, out, status)
+        if r is not None:
+            return r
     import torch
     _check_hist_sizes(hist)
     dev = hist.counts.device
@@ -381,6 +403,11 @@ def nll_grad(hist: Hist, model: Model, theta, objective=POISSON, precision=FP64,
              want_grad_w=False, free_mask=0, nll_out=None, grad_out=None, grad_w_out=None,
              status=None):
     """(L, dL/dtheta * seed, optional seed * dL/dw) as device tensors."""
+    if _fast is not None:
+        r = _fast.nll_grad(hist, model, theta, objective, precision, seed, want_grad_w, free_mask,
+                           nll_out, grad_out, grad_w_out, status)
+        if r is not None:
+            return r
     import torch
     _check_hist_sizes(hist)
     dev = hist.counts.device
@@ -414,6 +441,10 @@ def nll_fisher(hist: Hist, model: Model, theta, objective=POISSON, out=None, sta
     """Expected Hessian F = sum_i w_i c_i (dmu_i/dtheta)(dmu_i/dtheta)^T at
     theta as a device f64[P, P] tensor (c_i = 1/mu Poisson, 2/mu Pearson,
     2/n Neyman)."""
+    if _fast is not None:
+        r = _fast.nll_fisher(hist, model, theta, objective, out, status)
+        if r is not None:
+            return r
     import torch
     _check_hist_sizes(hist)
     dev = hist.counts.device
@@ -439,6 +470,10 @@ def fisher_covariance(fisher, objective=POISSON, free_mask=0, out=None, status=N
     matrix in `fisher` ([P, P] or [B, P, P], device f64); UP = 1/2 for the
     Poisson NLL, 1 for the chi-squares.  Returns (cov, status) with status
     1 where the free block is not positive definite (cov NaN there)."""
+    if _fast is not None:
+        r = _fast.fisher_covariance(fisher, objective, free_mask, out, status)
+        if r is not None:
+            return r
     import torch
     F = fisher
     if F.dtype != torch.float64 or F.dim() not in (2, 3) or F.shape[-1] != F.shape[-2]:
@@ -463,6 +498,11 @@ def nll_unbinned(events, lo, hi, model: Model, theta, weights=None, want_grad=Tr
     """Extended unbinned NLL  Lambda - sum_e w_e ln lambda(x_e)  of the events
     (device f64[n]) in [lo, hi] and, if want_grad, its gradient; device
     tensors (nll, grad or None)."""
+    if _fast is not None:
+        r = _fast.nll_unbinned(events, lo, hi, model, theta, weights, want_grad, nll_out, grad_out,
+                               status)
+        if r is not None:
+            return r
     import torch
     if not isinstance(events, torch.Tensor) or events.dtype != torch.float64 or events.dim() != 1:
         raise ValueError("events must be a 1-D f64 tensor")
@@ -537,6 +577,12 @@ def fit_batch(counts_concat, offsets, ranges, model: Model, theta0, objective=PO
     hessian_init: IDENTITY or FISHER (inverse expected Hessian at theta0);
     gradient: ADJOINT (reverse-mode sweep) or FINITE_DIFF (central
     differences of the objective, FP64 only)."""
+    if _fast is not None and out is None:
+        r = _fast.fit_batch(counts_concat, offsets, ranges, model, theta0, objective, precision,
+                            max_iter, ls_max, fixed_iters, free_mask, edm_tol, polish_edm,
+                            hessian_init, gradient, FitBatchResult)
+        if r is not None:
+            return r
     import torch
     c = counts_concat
     if not isinstance(c, torch.Tensor) or c.device.type != "cuda" or not c.is_contiguous():

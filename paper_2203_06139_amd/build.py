@@ -1,4 +1,5 @@
-"""Build libhistfit.so in-tree with hipcc for gfx950.
+"""Build libhistfit.so in-tree with hipcc for gfx950, and the binding's native
+marshalling module _fastcall.so (host code against torch's headers).
 
 Every translation unit under csrc/ is compiled in parallel to an object in
 _build/, then linked into paper_2203_06139_amd/libhistfit.so.  Always
@@ -17,6 +18,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhistfit.so")
+BINDING = os.path.join(HERE, "_fastcall.so")
 ARCH = os.environ.get("HF_OFFLOAD_ARCH", "gfx950")
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -59,6 +61,27 @@ def build(jobs: int | None = None, out: str = LIB, build_dir: str = BUILD, extra
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s%s" % (r.stdout, r.stderr))
+    os.replace(tmp, out)
+    if out == LIB:
+        build_binding()
+    return out
+
+
+def build_binding(out: str = BINDING) -> str:
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    tmp = out + ".tmp%d" % os.getpid()
+    libs = cpp_extension.library_paths(device_type="cuda")
+    cmd = [HIPCC, "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *("-isystem" + d for d in cpp_extension.include_paths(device_type="cuda")),
+           "-I" + sysconfig.get_path("include"), os.path.join(HERE, "binding", "fastcall.cpp"),
+           "-o", tmp, *("-L" + d for d in libs), *("-Wl,-rpath," + d for d in libs),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("building %s failed:\n%s%s" % (out, r.stdout, r.stderr))
     os.replace(tmp, out)
     return out
 
