@@ -153,6 +153,15 @@ struct Model1D {
   }
 };
 
+// final_factor where the Gaussians' sums were of e, e u and e u^2 (u =
+// kGaussU (x - m)/s, see gauss_n) without the amplitude; k a constant.
+template <int NG, int BKG>
+__device__ __forceinline__ double gauss_factor(const Model1D<NG, BKG>& M, int k) {
+  const double f = M.final_factor(k);
+  if (k < 1 || k > 3 * NG || (k - 1) % 3 == 0) return f;
+  return f * (M.A[(k - 1) / 3] * ((k - 1) % 3 == 1 ? kGaussUInv : kGaussUInv2));
+}
+
 // --------------------------------------------------------------------------
 // 2D correlated Gaussian + constant.
 // --------------------------------------------------------------------------

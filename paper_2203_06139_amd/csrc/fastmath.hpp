@@ -74,6 +74,12 @@ constexpr double kGaussULo = -2.59594641045974034667e-17;  // and its remainder
 constexpr double kGaussUInv = 1.17741002251547466351e+00;
 constexpr double kGaussUInv2 = 1.38629436111989057245e+00;
 
+// kGaussU / s to the last bit, from is = 1 / s.
+__device__ __forceinline__ double gauss_unit(double is, double s) {
+  const double q = kGaussU * is;
+  return fma(is, fma(-q, s, kGaussU) + kGaussULo, q);
+}
+
 template <int N>
 __device__ __forceinline__ void gauss_n(const double (&u)[N], double (&e)[N]) {
   constexpr double kRound = 6755399441055744.0;
@@ -207,26 +213,31 @@ __device__ __forceinline__ double log_lut(double x, const double2* __restrict__ 
 // Chebyshev interpolants computed in 60-digit arithmetic (truncation below
 // 1e-17).  Absolute error, against 50 digits: rms 3.5e-17, at most 1.1e-16, as
 // of the library's erf, which takes about 200 instructions to these 20 to 35.
-__device__ __forceinline__ double erf_from_phi(double z, double phi) {
+constexpr int kErfNear = 13, kErfFar = 16;  // coefficients, highest first
+static __device__ const double kErfCoef[kErfNear + kErfFar] = {
+    5.957176147748911e-11, -1.1372848856791674e-09, 1.4659775274047436e-08,
+    -1.6350312701054695e-07, 1.6461000484121368e-06, -1.4925595266831182e-05,
+    0.0001205533111164271, -0.000854832698083379, 0.0052239776248180145, -0.026866170645076792,
+    0.11283791670954879, -0.3761263890318375, 1.1283791670955126,
+    -2.279742613773115e-12, 5.830884699677111e-12, 8.098927716409088e-11, -2.9728506949500295e-10,
+    -2.942735833696472e-09, 1.1449481840693569e-08, 1.3353032032709014e-07,
+    -2.8199389473825003e-07, -7.246255012285937e-06, -1.608776475267465e-05,
+    0.00032354378790109227, 0.003933868783798848, 0.025474072799978032, 0.11683673753802074,
+    0.4118820962100305, 1.1519074596928367,
+};
+
+// c: kErfCoef in LDS.  As literals the coefficients outlive the scalar
+// registers and are held in 58 vector registers through the whole kernel.
+__device__ __forceinline__ double erf_from_phi(double z, double phi, const double* c) {
   const double x = fabs(z) * 0.70710678118654752440;
   double r;
   // neighbouring bins mostly fall on one side, so a wave takes one branch;
   // with both forms evaluated and selected 1e6 bins took 23.0 us, not 19.5
   if (x < 1.0) {
     const double w = x * x;
-    double p = 5.957176147748911e-11;
-    p = fma(p, w, -1.1372848856791674e-09);
-    p = fma(p, w, 1.4659775274047436e-08);
-    p = fma(p, w, -1.6350312701054695e-07);
-    p = fma(p, w, 1.6461000484121368e-06);
-    p = fma(p, w, -1.4925595266831182e-05);
-    p = fma(p, w, 0.0001205533111164271);
-    p = fma(p, w, -0.000854832698083379);
-    p = fma(p, w, 0.0052239776248180145);
-    p = fma(p, w, -0.026866170645076792);
-    p = fma(p, w, 0.11283791670954879);
-    p = fma(p, w, -0.3761263890318375);
-    p = fma(p, w, 1.1283791670955126);
+    double p = c[0];
+#pragma unroll
+    for (int k = 1; k < kErfNear; ++k) p = fma(p, w, c[k]);
     r = p * x;
   } else {
     const double xc = x > 6.0 ? 6.0 : x;  // keeps a NaN
@@ -234,25 +245,17 @@ __device__ __forceinline__ double erf_from_phi(double z, double phi) {
     double t = rcp_fast(d);
     t = fma(t, fma(-d, t, 1.0), t);
     const double u = fma(t, 14.4, -2.6);
-    double q = -2.279742613773115e-12;
-    q = fma(q, u, 5.830884699677111e-12);
-    q = fma(q, u, 8.098927716409088e-11);
-    q = fma(q, u, -2.9728506949500295e-10);
-    q = fma(q, u, -2.942735833696472e-09);
-    q = fma(q, u, 1.1449481840693569e-08);
-    q = fma(q, u, 1.3353032032709014e-07);
-    q = fma(q, u, -2.8199389473825003e-07);
-    q = fma(q, u, -7.246255012285937e-06);
-    q = fma(q, u, -1.608776475267465e-05);
-    q = fma(q, u, 0.00032354378790109227);
-    q = fma(q, u, 0.003933868783798848);
-    q = fma(q, u, 0.025474072799978032);
-    q = fma(q, u, 0.11683673753802074);
-    q = fma(q, u, 0.4118820962100305);
-    q = fma(q, u, 1.1519074596928367);
+    double q = c[kErfNear];
+#pragma unroll
+    for (int k = 1; k < kErfFar; ++k) q = fma(q, u, c[kErfNear + k]);
     r = fma(-q * t, phi, 1.0);
   }
   return __builtin_copysign(r, z);
+}
+
+// To LDS; the block must synchronise before the first use.
+__device__ __forceinline__ void erf_load(double* c) {
+  if (threadIdx.x < kErfNear + kErfFar) c[threadIdx.x] = kErfCoef[threadIdx.x];
 }
 
 // S(u) = sinh(u)/u and S'(u) = (cosh u - S(u))/u: the average of

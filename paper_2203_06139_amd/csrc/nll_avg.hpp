@@ -22,13 +22,15 @@
 // Each bin evaluates erf and exp at its right edge and hands them to the next
 // bin (a thread walking uniform bins edge to edge, or a wave taking 64 bins of
 // any widths side by side), so a bin costs one erf and one exp per Gaussian.
-// On uniform bins narrower
-// than a sixteenth of every width, the Gaussians' averages and partials come
-// instead from a Hermite series about the bin centre, with exp at the
-// centres by the two-multiply recurrence (no erf; see k_nll_1d_avg).  The objective terms, the
+// On bins narrower than a sixteenth of every width, the Gaussians' averages
+// and partials come instead from a Hermite series about the bin centre, on
+// uniform bins with exp at the centres by the two-multiply recurrence (no
+// erf; see k_nll_1d_avg).  The objective terms, the
 // reverse sweep (w ubar times the partials above) and the reduction are the
 // centre model's.  FP64 only.
 #pragma once
+
+#include <type_traits>
 
 #include "chunk.hpp"
 #include "nll_kernels.hpp"
@@ -75,6 +77,8 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
   constexpr double kRt = 1.2533141373155002512;   // sqrt(pi/2)
   __shared__ double2 lut[OBJ == OBJ_POISSON ? kLogLut : 1];
   if constexpr (OBJ == OBJ_POISSON) log_lut_load(lut, a.log_lut);
+  __shared__ double ec[kErfNear + kErfFar];
+  erf_load(ec);
   Model1D<NG, BKG> M;
   M.init(a.theta, a.t_shift, a.t_scale);
   double sg[G1];
@@ -112,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
       cs[g][k] = cs[g][k - 1] * d2 / static_cast<double>((2 * k) * (2 * k + 1));
   }
   const int nh = dmax <= 4.5e-6 ? 1 : (dmax <= 1.6e-3 ? 3 : kHermMax);
-  if constexpr (OBJ == OBJ_POISSON) __syncthreads();
+  __syncthreads();
   double acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
       for (int g = 0; g < NG; ++g) {
         za[g] = (x - M.m[g]) * M.is[g];
         ea[g] = exp_fast(-0.5 * za[g] * za[g]);
-        Ea[g] = erf_from_phi(za[g], ea[g]);
+        Ea[g] = erf_from_phi(za[g], ea[g], ec);
       }
     }
     // the next bin's count and weight are requested while the current bin is
@@ -153,6 +157,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
     double n_nx = load_count1(a, i0);
     double w_nx = a.weights ? static_cast<double>(a.weights[i0]) : 1.0;
     for (int k = 0; k < len; ++k) {
+      asm volatile("" ::: "memory");  // the coefficients are read again
       const int64_t i = i0 + k;
       const double n = n_nx, w = w_nx;
       const double xb = fma(static_cast<double>(i + 1), a.hx, a.x0);
@@ -191,7 +196,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
         for (int g = 0; g < NG; ++g) {
           const double zb = (xb - M.m[g]) * M.is[g];
           const double eb = exp_fast(-0.5 * zb * zb);
-          const double Eb = erf_from_phi(zb, eb);
+          const double Eb = erf_from_phi(zb, eb, ec);
           const double ia = sg[g] * kRt * (Eb - Ea[g]) * ih;
           const double mg = M.A[g] * ia;
           mu += mg;
@@ -260,17 +265,24 @@ __device__ __forceinline__ double from_previous_lane(double x, double first) {
   return __hiloint2double(hi, lo);
 }
 
-// Bins of any widths.  A wave takes 64 neighbouring bins per step, each lane
-// evaluating erf and exp at its bin's right edge; the left edge's values come
-// from the lane before by a DPP move, and lane 0's from the last lane of the
-// step before (a wave's steps are consecutive; it evaluates one more edge at
-// its start).  So loads are contiguous and a bin still costs one erf and exp
-// per Gaussian.
-// Bound: VALU issue.  Two Gaussians and a line, Poisson, on the GPU with the
-// finishing kernel, against a thread walking 8 bins edge to edge with the
-// library's erf: 1003 bins 14.9 -> 7.7 us (the chain of 8 bins is gone),
-// 100,003 bins 14.9 -> 9.2, 1e6 bins 20.4 -> 19.5, 4e6 bins 61.3 -> 58.8.  Two
-// steps side by side were slower (24 us at 1e6): registers, not latency.
+// Bins of any widths.  A wave takes 64 neighbouring bins per step.
+// Where all of them are narrow against every Gaussian's width (h <= s / 16),
+// the averages come from the series about the bins' centres that
+// k_nll_1d_avg explains, with 2, 3 or 6 terms after the first by the widest
+// bin of the step (2 keep the first omitted term below 1e-19 for half-widths
+// up to 2.1e-4 s).  It needs no erf, no division and no neighbour, and has
+// none of the cancellation of an erf difference over a narrow bin.
+// Elsewhere each lane evaluates erf and exp at its bin's right edge; the left
+// edge's values come from the lane before by a DPP move, and lane 0's from the
+// last lane of the step before.  So loads are contiguous and a bin costs one
+// erf and exp per Gaussian.
+// Bound: VALU issue, about 240 instructions per bin.  Two Gaussians and a
+// line, Poisson, on the GPU with the finishing kernel: a thread walking 8 bins
+// edge to edge with the library's erf 20.4 us for 1e6 bins and 61.3 for 4e6;
+// 64 bins per wave with erf 19.0 and 58.4; with the series 15.4 and 43.3.
+// 1003 bins 14.9, 7.4 and 7.9.  Two steps side by side gain nothing (15.9 and
+// 45.6 with 244 registers), nor does room for a third wave (17.8 and 47.1 with
+// 10 spills).
 template <int NG, int BKG, int OBJ, bool GRAD>
 __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
   using S = Shape1D<NG, BKG>;
@@ -280,12 +292,14 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
   constexpr double kRt = 1.2533141373155002512;   // sqrt(pi/2)
   __shared__ double2 lut[OBJ == OBJ_POISSON ? kLogLut : 1];
   if constexpr (OBJ == OBJ_POISSON) log_lut_load(lut, a.log_lut);
+  __shared__ double ec[kErfNear + kErfFar];
+  erf_load(ec);
   Model1D<NG, BKG> M;
   M.init(a.theta, a.t_shift, a.t_scale);
   double sg[G1];
 #pragma unroll
   for (int g = 0; g < NG; ++g) sg[g] = a.theta[3 * g + 2];
-  if constexpr (OBJ == OBJ_POISSON) __syncthreads();
+  __syncthreads();
   double acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;
@@ -300,22 +314,32 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
   const int lane = static_cast<int>(threadIdx.x & 63u);
   const int64_t s0 = steps * wave / waves, s1 = steps * (wave + 1) / waves;
   if (s0 < s1) {
-    // position, z, erf and phi at an edge
+    double us[G1], ismax = 0.0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      us[g] = gauss_unit(M.is[g], sg[g]);
+      ismax = fmax(ismax, fabs(M.is[g]));
+    }
+    // z, erf and phi at an edge
     struct Edge {
-      double x, z[G1], E[G1], e[G1];
+      double z[G1], E[G1], e[G1];
     };
     auto edge = [&](double x) {
       Edge r;
-      r.x = x;
+      double u[G1];
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         r.z[g] = (x - M.m[g]) * M.is[g];
-        r.e[g] = exp_fast(-0.5 * r.z[g] * r.z[g]);
-        r.E[g] = erf_from_phi(r.z[g], r.e[g]);
+        u[g] = (x - M.m[g]) * us[g];
       }
+      if constexpr (NG > 0) gauss_n(u, r.e);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) r.E[g] = erf_from_phi(r.z[g], r.e[g], ec);
       return r;
     };
-    Edge last = edge(E[64 * s0]);  // right edge of the bin before the step
+    double x_last = E[64 * s0];  // right edge of the bin before the step
+    Edge last;                   // and its values, where last_set
+    bool last_set = false;
     auto bin = [&](int64_t s) {
       const int64_t i = 64 * s + lane;
       return i < nb ? i : nb - 1;
@@ -326,47 +350,91 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
     for (int64_t s = s0; s < s1; ++s) {
       const int64_t i = i_nx;
       const bool in = 64 * s + lane < nb;  // lanes past the last bin compute it again and are dropped
-      const double n = n_nx, w = w_nx;
-      const Edge right = edge(x_nx);
+      const double n = n_nx, w = w_nx, xb = x_nx;
       if (s + 1 < s1) {
         i_nx = bin(s + 1);
         x_nx = E[i_nx + 1];
         n_nx = load_count1(a, i_nx);
         w_nx = a.weights ? static_cast<double>(a.weights[i_nx]) : 1.0;
       }
-      const double xa = from_previous_lane(right.x, last.x), xb = right.x;
-      const double ih = in ? 1.0 / (xb - xa) : 0.0;
+      const double x_first = x_last, xa = from_previous_lane(xb, x_last);
+      x_last = readlane_d(xb, 63);
+      const double h = xb - xa, xc = 0.5 * (xa + xb);
       double mu = 0.0;
       double J[P];
+      // the series about the centre (see k_nll_1d_avg)
+      auto series = [&](auto terms) {
+        constexpr int NH = decltype(terms)::value;
+        double u[G1], e[G1];
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const double Ea = from_previous_lane(right.E[g], last.E[g]);
-        const double ia = sg[g] * kRt * (right.E[g] - Ea) * ih;
-        const double mg = M.A[g] * ia;
-        mu += mg;
-        if constexpr (GRAD) {
-          const double za = from_previous_lane(right.z[g], last.z[g]);
-          const double ea = from_previous_lane(right.e[g], last.e[g]);
-          J[3 * g] = ia;
-          J[3 * g + 1] = M.A[g] * (ea - right.e[g]) * ih;
-          J[3 * g + 2] = fma(mg, M.is[g], M.A[g] * fma(za, ea, -right.z[g] * right.e[g]) * ih);
+        for (int g = 0; g < NG; ++g) u[g] = (xc - M.m[g]) * us[g];
+        if constexpr (NG > 0) gauss_n(u, e);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          const double z = (xc - M.m[g]) * M.is[g], d = 0.5 * h * M.is[g], d2 = d * d;
+          double c[kHermMax + 1];
+          c[0] = 1.0;
+#pragma unroll
+          for (int k = 1; k <= NH; ++k)
+            c[k] = c[k - 1] * (d2 * (1.0 / static_cast<double>((2 * k) * (2 * k + 1))));
+          double sv, tv, ux;
+          herm_series<NH>(z, c, sv, tv, ux);
+          const double es = e[g] * sv;
+          mu = fma(M.A[g], es, mu);
+          if constexpr (GRAD) {
+            const double ae = M.A[g] * M.is[g] * e[g];
+            J[3 * g] = es;
+            J[3 * g + 1] = ae * tv;
+            J[3 * g + 2] = ae * (sv + ux);
+          }
+        }
+      };
+      const double dmax = 0.5 * fabs(h) * ismax;
+      // (an empty bin, or an edge or width that is no number: as the erf says)
+      const bool small = NG > 0 && __all(!in || (h != 0.0 && dmax <= 1.0 / 32.0));
+      if (small) {
+        last_set = false;
+        if (__all(!in || dmax <= 2.1e-4))
+          series(std::integral_constant<int, 2>{});
+        else if (__all(!in || dmax <= 1.6e-3))
+          series(std::integral_constant<int, 3>{});
+        else
+          series(std::integral_constant<int, kHermMax>{});
+      } else {
+        asm volatile("" ::: "memory");  // the coefficients are read again
+        if (!last_set) last = edge(x_first);
+        last_set = true;
+        const Edge right = edge(xb);
+        const double ih = in ? 1.0 / h : 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          const double Ea = from_previous_lane(right.E[g], last.E[g]);
+          const double ia = sg[g] * kRt * (right.E[g] - Ea) * ih;
+          const double mg = M.A[g] * ia;
+          mu = fma(M.A[g], ia, mu);
+          if constexpr (GRAD) {
+            const double za = from_previous_lane(right.z[g], last.z[g]);
+            const double ea = from_previous_lane(right.e[g], last.e[g]);
+            J[3 * g] = ia;
+            J[3 * g + 1] = M.A[g] * (ea - right.e[g]) * ih;
+            J[3 * g + 2] = fma(mg, M.is[g], M.A[g] * fma(za, ea, -right.z[g] * right.e[g]) * ih);
+          }
+        }
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          last.z[g] = readlane_d(right.z[g], 63);
+          last.E[g] = readlane_d(right.E[g], 63);
+          last.e[g] = readlane_d(right.e[g], 63);
         }
       }
-      last.x = readlane_d(right.x, 63);
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        last.z[g] = readlane_d(right.z[g], 63);
-        last.E[g] = readlane_d(right.E[g], 63);
-        last.e[g] = readlane_d(right.e[g], 63);
-      }
-      const double tc = (0.5 * (xa + xb) - M.tshift) * M.ta;
-      const double dh = 0.5 * (xb - xa) * M.ta;
+      const double tc = (xc - M.tshift) * M.ta;
+      const double dh = 0.5 * h * M.ta;
       if constexpr (BKG == BKG_EXP) {
         const double Ec = exp_fast(fma(M.c[1], tc, M.c[0]));
         double Sh, dSh;
         sinhc(M.c[1] * dh, Sh, dSh);
         const double eb = Ec * Sh;
-        mu += eb;
+        mu = fma(Ec, Sh, mu);
         if constexpr (GRAD) {
           J[3 * NG] = eb;
           J[3 * NG + 1] = Ec * fma(tc, Sh, dh * dSh);
@@ -406,9 +474,10 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
 // closed-form partials (A: e; m: G z; s: G z^2, the 1/s applied to the
 // totals; polynomial t^j; exponential E and t E), one exp per Gaussian.
 // A thread takes kEdgeChunk consecutive bins per step (their kEdgeChunk + 1
-// edges are shared between neighbours), computed together so that their
-// exp chains interleave, and requests the next step's edges, counts and
-// weights while the current step is computed.
+// edges are shared between neighbours), their exponentials in step, and
+// requests the next step's edges, counts and weights while the current step
+// is computed.  Two Gaussians and a line, Poisson, 4e6 bins: 28.5 us on the
+// GPU, with one exponential after the other 30.6 (1e6: 12.2 and 13.1).
 constexpr int kEdgeChunk = 4;
 
 struct EdgeChunk {
@@ -436,6 +505,9 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_edges(NllArgs a) {
   if constexpr (OBJ == OBJ_POISSON) log_lut_load(lut, a.log_lut);
   Model1D<NG, BKG> M;
   M.init(a.theta, a.t_shift, a.t_scale);
+  double us[NG > 0 ? NG : 1];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) us[g] = gauss_unit(M.is[g], a.theta[3 * g + 2]);
   if constexpr (OBJ == OBJ_POISSON) __syncthreads();
   double acc[NV];
 #pragma unroll
@@ -460,25 +532,30 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_edges(NllArgs a) {
       const int64_t j0 = (c + stride) * K;
       load_edge_chunk(a, j0, static_cast<int>(nb - j0 < K ? nb - j0 : K), nxt);
     }
+    // bins past len (the last chunk) are computed at a valid point and
+    // masked: their weight is 0 and their terms are dropped
+    double xk[K], u[NG > 0 ? NG * K : 1], ek[NG > 0 ? NG * K : 1];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      xk[k] = k < len ? 0.5 * (cur.e[k] + cur.e[k + 1]) : cur.e[0];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) u[NG * k + g] = (xk[k] - M.m[g]) * us[g];
+    }
+    if constexpr (NG > 0) gauss_n(u, ek);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       const bool in = k < len;
-      // bins past len (the last chunk) are computed at a valid point and
-      // masked: their weight is 0 and their terms are dropped
-      const double x = in ? 0.5 * (cur.e[k] + cur.e[k + 1]) : cur.e[0];
+      const double x = xk[k];
       double mu = 0.0;
       double J[P];
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        const double z = (x - M.m[g]) * M.is[g];
-        const double e = exp_fast(-0.5 * z * z);
-        const double G = M.A[g] * e;
-        mu += G;
-        if constexpr (GRAD) {
-          const double Gz = G * z;
+        const double e = ek[NG * k + g], uk = u[NG * k + g];
+        mu = fma(M.A[g], e, mu);
+        if constexpr (GRAD) {  // the amplitude and the width: on the totals
           J[3 * g] = e;
-          J[3 * g + 1] = Gz;
-          J[3 * g + 2] = Gz * z;
+          J[3 * g + 1] = e * uk;
+          J[3 * g + 2] = e * uk * uk;
         }
       }
       const double t = (x - M.tshift) * M.ta;
@@ -517,7 +594,10 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_edges(NllArgs a) {
     }
   }
   __shared__ double fac[NV];
-  if (threadIdx.x < NV) fac[threadIdx.x] = M.final_factor(threadIdx.x);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) fac[k] = gauss_factor(M, k);
+  }
   publish_objective<NV>(a, acc, flags | (finite ? 0 : ST_NONFINITE), fac, output_seed(a));
 }
 
@@ -566,9 +646,12 @@ LaunchFn pick_edges_ng(int bkg, int obj, bool grad) {
 
 template <int NG, int BKG, int OBJ, bool GRAD, bool EDGES>
 hipError_t launch_1d_avg(const NllArgs& a, int grid, hipStream_t s, int* occ, int* block) {
-  if constexpr (EDGES)
+  if constexpr (EDGES) {
+    // the value alone takes the gradient's grid, for the same sums
+    if (grid <= 0)
+      return launch_or_occupancy<kBlock>(k_nll_1d_avg_edges<NG, BKG, OBJ, true>, a, grid, s, occ, block);
     return launch_or_occupancy<kBlock>(k_nll_1d_avg_edges<NG, BKG, OBJ, GRAD>, a, grid, s, occ, block);
-  else
+  } else
     return launch_or_occupancy<kBlock>(k_nll_1d_avg<NG, BKG, OBJ, GRAD>, a, grid, s, occ, block);
 }
 

@@ -254,20 +254,12 @@ __global__ __launch_bounds__(kBlock, kUbWaves<NG>) void k_nll_unbinned(UnbinnedA
   if (threadIdx.x == 0) {
     if (blockIdx.x == 0) lambda_terms<NG, BKG>(a, M, lamd);
 #pragma unroll
-    for (int k = 0; k <= S::P; ++k) {
-      ff[k] = M.final_factor(k);
-      if (k >= 1 && k <= 3 * NG && (k - 1) % 3 != 0)
-        ff[k] *= M.A[(k - 1) / 3] * ((k - 1) % 3 == 1 ? kGaussUInv : kGaussUInv2);
-    }
+    for (int k = 0; k <= S::P; ++k) ff[k] = gauss_factor(M, k);
   }
   __syncthreads();
   double us[NG > 0 ? NG : 1];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    // kGaussU / s to the last bit
-    const double s = a.theta[3 * g + 2], q = kGaussU * M.is[g];
-    us[g] = fma(M.is[g], fma(-q, s, kGaussU) + kGaussULo, q);
-  }
+  for (int g = 0; g < NG; ++g) us[g] = gauss_unit(M.is[g], a.theta[3 * g + 2]);
   double acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;

@@ -44,3 +44,36 @@ def test_average_in_the_tails(hf, orc):
     nll, grad, _, st, _ = gpu(hf, spec, counts, e, at, 2, avg=1)
     check(ref, nll, grad, "tails")
     assert st == 0
+
+
+@pytest.mark.parametrize("half", [1e-6, 2.0e-4, 2.2e-4, 1.5e-3, 1.7e-3, 0.031, 0.032, 0.2])
+def test_average_series(hf, orc, half):
+    """Bins of half-widths around the limits of each series (in units of the
+    narrowest width), and steps that mix them with wide ones."""
+    spec, _, _ = CASES[1]
+    th = [700.0, 4.8, 0.4, 400.0, 5.2, 0.6, 100.0, -20.0, 10.0, 5.0]
+    rng = np.random.default_rng(int(half * 1e7))
+    n = 1000
+    h = 2.0 * half * 0.4 * rng.uniform(0.9, 1.0, n)
+    if half == 1.5e-3:
+        h[[70, 200, 201, 640]] = [0.05, 0.5, 1e-5, 0.2]
+    e = 4.0 + np.concatenate([[0.0], np.cumsum(h)])
+    e = e[e < 9.9]
+    counts = counts_for(orc, spec, e, th, 1, seed=5)
+    ref = orc.nll_grad_edges(orc_model(orc, spec, 1), 2, counts, e, th, want_ell=True)
+    nll, grad, gw, st, ev = gpu(hf, spec, counts, e, th, 2, avg=1, want_grad_w=True)
+    # the oracle's erf differences lose about 2.3e-16 / half per bin
+    tol = 1e-10 + 4.0 * 2.3e-16 / half
+    assert st == ref.status == 0 and ev == nll
+    assert abs(nll - ref.nll) <= tol * ref.scales[0]
+    assert np.all(np.abs(grad - ref.grad) <= tol * ref.scales[1:])
+
+
+def test_average_degenerate_bins(hf):
+    """An empty bin is no number, with or without narrow bins beside it."""
+    spec, th, _ = CASES[1]
+    for n in (3, 64, 200):
+        e = np.linspace(2.0, 2.001, n + 1)
+        e[n // 2 + 1] = e[n // 2]
+        nll, grad, _, st, _ = gpu(hf, spec, np.ones(n, dtype=np.uint32), e, th, 2, avg=1)
+        assert st == 0 and np.isnan(nll) and np.isnan(grad).any()
