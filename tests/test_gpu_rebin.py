@@ -26,3 +26,18 @@ def test_rebin_lane_counts(hf, dtype):
     x = hf.rebin_lognorm(torch.from_numpy(counts.astype(cast)).cuda(), torch.from_numpy(offsets).cuda(),
                          1.5, 2.0).cpu().numpy()
     np.testing.assert_allclose(x, ref, rtol=2.0 ** -23, atol=1.5 * 2.0 ** -23)
+
+
+@pytest.mark.parametrize("n", [2 ** 21 - 1, 2 ** 21, 2 ** 21 + 1, 5_000_011])
+def test_rebin_long_histograms(hf, n):
+    """Either side of the length from which positions take 64 bits; the same
+    bound."""
+    import torch
+
+    import oracle.mlp as om
+    counts = np.random.default_rng(n).integers(0, 1000, n + 3).astype(np.int32)
+    offsets = np.array([0, 3, n + 3], dtype=np.int64)
+    ref = om.rebin_lognorm(counts.astype(np.uint32), offsets, 1.5, 2.0)
+    x = hf.rebin_lognorm(torch.from_numpy(counts).cuda(), torch.from_numpy(offsets).cuda(),
+                         1.5, 2.0).cpu().numpy()
+    np.testing.assert_allclose(x, ref, rtol=2.0 ** -23, atol=1.5 * 2.0 ** -23)
