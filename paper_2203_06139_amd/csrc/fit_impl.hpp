@@ -57,7 +57,7 @@ struct FitShared {
   static constexpr int P = Shape1D<NG, BKG>::P;
   static constexpr int NV = P + 1;
   double th[P], th0[P], sig[P];
-  double u[P], g[P], un[P], gn[P], pv[P], tmp[P], sv[P], yv[P], Hy[P], up[P];
+  double u[P], g[P], un[P], gn[P], pv[P], up[P];
   double H[P * P];   // row stride P; the leading nf x nf block is used
   double tot[NV];
   double red[BLK / 64][NV];
@@ -602,22 +602,17 @@ __device__ __forceinline__ bool fisher_start(FitShared<NG, BKG, BLK>& sm, int nf
   return ok;
 }
 
-// Sum over q < n of x[q] y[q] (or of x[q] when y is null), in order of q.
-// The first P entries are loaded up front, so the LDS reads overlap instead
-// of making one round trip per term.
+// Sum over the first 16 lanes, wave-uniform.
+__device__ __forceinline__ double lane_sum(double v) { return readlane_d(row_sum(v), 0); }
+
+// Row of H (one per lane) times the vector whose entries the lanes hold: four
+// partial sums, so that the chain is P / 4 + 2 operations long.
 template <int P>
-__device__ __forceinline__ double dot_lds(const double* x, const double* y, int n) {
-  double v[P], w[P];
+__device__ __forceinline__ double row_times(const double (&h)[P], double v) {
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int q = 0; q < P; ++q) {
-    v[q] = x[q];
-    w[q] = y ? y[q] : 1.0;
-  }
-  double s = 0.0;
-#pragma unroll
-  for (int q = 0; q < P; ++q)
-    if (q < n) s = fma(v[q], w[q], s);
-  return s;
+  for (int c = 0; c < P; ++c) s[c & 3] = fma(h[c], readlane_d(v, c), s[c & 3]);
+  return (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 // Central differences in the scaled coordinates, the gradient a fitter
@@ -759,69 +754,67 @@ __device__ __forceinline__ void optimiser_step(const FitArgs& a, FitShared<NG, B
     if (lane < nf) sm.up[lane] = lane == q ? uq + h : sm.un[lane];
     return optimiser_point(a, sm, EV_FD_PLUS, false);
   }
-  // gradient at the new point, in the scaled coordinates
+  // gradient at the new point, in the scaled coordinates.  Lane q < nf holds
+  // entry q of every vector and row q of H; the other lanes hold zeros, and
+  // rows of H that are never written.  What passes between lanes goes by DPP
+  // and readlane, not through LDS in sums of P terms one after the other: one
+  // fit of 10,000 bins 77.3 -> 74.6 us, 512 fits of three Gaussians 309 -> 298.
+  const bool mine = lane < nf;
   double gq = 0.0;
-  if (lane < nf) gq = fd ? sm.gn[lane] : sm.sig[sm.fidx[lane]] * sm.tot[1 + sm.fidx[lane]];
+  if (mine) gq = fd ? sm.gn[lane] : sm.sig[sm.fidx[lane]] * sm.tot[1 + sm.fidx[lane]];
+  double h[P];
+#pragma unroll
+  for (int c = 0; c < P; ++c) h[c] = sm.H[(mine ? lane : 0) * P + c];
+  const double un = mine ? sm.un[lane] : 0.0;
   if (accepted) {
-    if (lane < nf) {
-      sm.sv[lane] = sm.un[lane] - sm.u[lane];
-      sm.yv[lane] = gq - sm.g[lane];
-    }
+    const double sv = mine ? un - sm.u[lane] : 0.0, yv = mine ? gq - sm.g[lane] : 0.0;
     f = fd && nf > 0 ? sm.fn : fe;
-    gsync<64>();
-    const double sy = dot_lds<P>(sm.sv, sm.yv, nf);
-    const double yy = dot_lds<P>(sm.yv, sm.yv, nf);
-    const double ss = dot_lds<P>(sm.sv, sm.sv, nf);
+    const double sy = lane_sum(sv * yv), yy = lane_sum(yv * yv), ss = lane_sum(sv * sv);
     if (sy > 1e-12 * sqrt(ss) * sqrt(yy)) {
       if (sm.first) {
         const double gam = sy / yy;
+#pragma unroll
+        for (int c = 0; c < P; ++c) h[c] *= gam;
         gsync<64>();
-        for (int t = lane; t < nf * nf; t += 64) sm.H[(t / nf) * P + t % nf] *= gam;
         if (lane == 0) sm.first = 0;
-        gsync<64>();
       }
-      if (lane < nf) sm.Hy[lane] = dot_lds<P>(&sm.H[lane * P], sm.yv, nf);
-      gsync<64>();
-      const double yHy = dot_lds<P>(sm.yv, sm.Hy, nf);
       const double rho = 1.0 / sy;
-      const double cc = rho * rho * yHy + rho;
-      for (int t = lane; t < nf * nf; t += 64) {
-        const int r = t / nf, c = t % nf;
-        sm.H[r * P + c] += -rho * (sm.Hy[r] * sm.sv[c] + sm.sv[r] * sm.Hy[c]) + cc * sm.sv[r] * sm.sv[c];
+      const double Hy = row_times<P>(h, yv);
+      const double cc = rho * rho * lane_sum(yv * Hy) + rho;
+#pragma unroll
+      for (int c = 0; c < P; ++c) {
+        const double sc = readlane_d(sv, c), Hc = readlane_d(Hy, c);
+        h[c] += -rho * (Hy * sc + sv * Hc) + cc * sv * sc;
+        if (mine) sm.H[lane * P + c] = h[c];
       }
     }
   }
-  if (lane < nf) {
-    sm.u[lane] = sm.un[lane];
+  gsync<64>();
+  if (mine) {
+    sm.u[lane] = un;
     sm.g[lane] = gq;
   }
   if (lane == 0) sm.f = f;
-  gsync<64>();
   // direction p = -H g
   if (sm.it < a.max_iter) {
-    if (lane < nf) {
-      const double hg = dot_lds<P>(&sm.H[lane * P], sm.g, nf);
-      sm.pv[lane] = -hg;
-      sm.tmp[lane] = sm.g[lane] * hg;
-    }
-    gsync<64>();
-    const double edm = 0.5 * dot_lds<P>(sm.tmp, nullptr, nf);
+    double pv = mine ? -row_times<P>(h, gq) : 0.0;
+    double slope = lane_sum(gq * pv);
+    const double edm = -0.5 * slope;
     const double goal = fmax(a.edm_tol, 4.0 * DBL_EPSILON * fabs(f));
     if (f32 && a.polish_edm > 0.0 && edm < a.polish_edm) {
       // switch to FP64 bins for the rest of the fit, at sm.un = sm.u
       if (lane == 0) ++sm.nev;
+      if (mine) sm.pv[lane] = pv;
       return optimiser_point(a, sm, EV_POLISH, false);
     }
     if (!a.fixed_iters && edm < goal) {
       if (lane == 0) sm.status = FIT_CONVERGED;
     } else {
-      double slope = dot_lds<P>(sm.g, sm.pv, nf);
       if (!(slope < 0.0)) {  // H lost positive definiteness: restart from I
-        gsync<64>();
         for (int t = lane; t < P * P; t += 64) sm.H[t] = (t / P == t % P) ? 1.0 : 0.0;
-        if (lane < nf) sm.pv[lane] = -sm.g[lane];
+        pv = -gq;
         if (lane == 0) sm.first = 1;
-        slope = -dot_lds<P>(sm.g, sm.g, nf);
+        slope = -lane_sum(gq * gq);
       }
       if (lane == 0) {
         sm.edm = edm;
@@ -830,7 +823,10 @@ __device__ __forceinline__ void optimiser_step(const FitArgs& a, FitShared<NG, B
         sm.alpha = 1.0;
         sm.ls = 0;
       }
-      if (lane < nf) sm.un[lane] = sm.u[lane] + sm.pv[lane];
+      if (mine) {
+        sm.pv[lane] = pv;
+        sm.un[lane] = un + pv;
+      }
       return optimiser_point(a, sm, EV_SEARCH, f32);
     }
     gsync<64>();
