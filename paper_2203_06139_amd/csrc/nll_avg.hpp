@@ -279,10 +279,10 @@ __device__ __forceinline__ double from_previous_lane(double x, double first) {
 // Bound: VALU issue, about 240 instructions per bin.  Two Gaussians and a
 // line, Poisson, on the GPU with the finishing kernel: a thread walking 8 bins
 // edge to edge with the library's erf 20.4 us for 1e6 bins and 61.3 for 4e6;
-// 64 bins per wave with erf 19.0 and 58.4; with the series 15.4 and 43.3.
-// 1003 bins 14.9, 7.4 and 7.9.  Two steps side by side gain nothing (15.9 and
-// 45.6 with 244 registers), nor does room for a third wave (17.8 and 47.1 with
-// 10 spills).
+// 64 bins per wave with erf 19.0 and 58.4; with the series 15.4 and 43.3, and
+// 15.2 and 38.9 without constants held in registers (build.py, NO_HOIST).
+// 1003 bins 14.9, 7.4 and 7.6.  Two steps side by side gain nothing (15.9 and
+// 45.6 with 244 registers).
 template <int NG, int BKG, int OBJ, bool GRAD>
 __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
   using S = Shape1D<NG, BKG>;
