@@ -154,7 +154,7 @@ hipError_t rebin_lognorm(int B, const void* counts, int dtype, const int64_t* of
 //     of counts over [i - W, i + W] (first such i on ties);
 //   width: walking out from the peak while 2 e >= e_max, the half-maximum
 //     bounds give the FWHM.
-// The window positions are split among the block's four waves in
+// The window positions are split among the block's waves in
 // contiguous ranges; a wave walks its range 64 positions per step, lane l
 // at position s + l, with coalesced loads: the window sum at position i is
 // the sum at the range's first position plus the lane prefix sum of the
@@ -202,25 +202,61 @@ __device__ __forceinline__ void window_walk(const void* counts, int dtype, int64
   }
 }
 
-// Threads per histogram: 16 waves (a histogram of 65,536 bins walks 64
-// steps of 64 positions per wave and pass).  Measured on the 4096-histogram
-// Gauss + exponential batch: 0.89 ms with 16 waves, 0.91 ms with four, and
-// 2.86 ms when each thread walked its own segment of positions with
-// scattered loads.  Per position the background's exp and the division
-// before it now dominate; both stay, since the excess must round as the
-// direct evaluation does.
-constexpr int kDsThreads = 1024;
-constexpr int kDsWaves = kDsThreads / 64;
+// The same sums for u32 counts, which are integers: exact in any order, so the
+// prefix goes by DPP, and the next step's counts are requested ahead.  fn(S, i,
+// in) is called by the whole wave.
+__device__ __forceinline__ double wave_prefix(double d) {
+  const int row = static_cast<int>(threadIdx.x & 63u) >> 4;
+  d += dpp_row<0x111>(d);  // row_shr:1, 2, 4, 8
+  d += dpp_row<0x112>(d);
+  d += dpp_row<0x114>(d);
+  d += dpp_row<0x118>(d);
+  const double a = readlane_d(d, 15), ab = a + readlane_d(d, 31), abc = ab + readlane_d(d, 47);
+  return d + (row == 0 ? 0.0 : row == 1 ? a : row == 2 ? ab : abc);
+}
 
-__global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* counts, int dtype,
+template <class Fn>
+__device__ __forceinline__ void window_walk_u32(const uint32_t* __restrict__ c, int64_t q0, int64_t q1,
+                                                int64_t W, Fn fn) {
+  if (q0 >= q1) return;
+  const int lane = static_cast<int>(threadIdx.x & 63u);
+  double s0 = 0.0;
+  for (int64_t q = q0 - W + lane; q <= q0 + W; q += 64) s0 += c[q];
+  double carry = wave_sum(s0);  // S(q0), then S of the previous step's last position
+  auto step = [&](int64_t i) {  // S(i) - S(i - 1)
+    return i > q0 && i < q1 ? static_cast<double>(c[i + W]) - static_cast<double>(c[i - W - 1]) : 0.0;
+  };
+  double next = step(q0 + lane);
+  for (int64_t base = q0; base < q1; base += 64) {
+    const int64_t i = base + lane;
+    const double S = carry + wave_prefix(next);
+    next = step(i + 64);
+    fn(S, i, i < q1);
+    carry = readlane_d(S, 63);
+  }
+}
+
+// T threads per histogram.  U32 (u32 counts): 512, which the registers of its
+// estimates allow two blocks per CU; otherwise 1024, with the walk above.
+// 4096 histograms of 256..65536 bins: 2.86 ms when each thread walked its own
+// segment of positions with scattered loads, 0.88 ms with 16 waves and every
+// excess (an exp and a division) rounded as the direct evaluation does, twice;
+// 0.47 ms with the excess only where an estimate leaves it a chance, and the
+// width searched outwards from the peak.  4096 of 10,000 bins 537 -> 275 us,
+// 1024 of 64..512 54.9 -> 29.0.  With 1024 threads one block fits a CU (670,
+// 458, 66.7), with spills two (884, 581, 79.2); 256 threads take 476, 231 and
+// 22.2, but 251 us instead of 160 for 64 histograms of 65,536.
+template <int T, bool U32>
+__global__ __launch_bounds__(T, 4) void k_default_starts(const void* counts, int dtype,
                                                                const int64_t* __restrict__ offsets,
                                                                const double* __restrict__ ranges,
                                                                double t_shift, double t_scale,
                                                                double* __restrict__ theta0) {
-  __shared__ double red_d[2][kDsWaves];
-  __shared__ int64_t red_e[kDsWaves];
-  __shared__ int64_t red_i[kDsWaves];
-  __shared__ int64_t red_j[kDsWaves];
+  constexpr int kWavesDs = T / 64;
+  __shared__ double red_d[2][kWavesDs];
+  __shared__ int64_t red_e[kWavesDs];
+  __shared__ int64_t red_i[kWavesDs];
+  __shared__ int64_t red_j[kWavesDs];
   const int b = blockIdx.x;
   const int t = threadIdx.x;
   const int lane = t & 63, wv = t >> 6;
@@ -235,7 +271,7 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
   const int64_t ne = nb / 25 > 0 ? nb / 25 : 1;  // 4% of the bins at each edge
   // edge sums (integer-valued: exact in any order)
   double sl = 0.0, sr = 0.0;
-  for (int64_t i = t; i < ne; i += kDsThreads) {
+  for (int64_t i = t; i < ne; i += T) {
     sl += count_any(counts, dtype, off + i);
     sr += count_any(counts, dtype, off + nb - ne + i);
   }
@@ -251,7 +287,7 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
   __syncthreads();
   double esl = 0.0, esr = 0.0;
 #pragma unroll
-  for (int w = 0; w < kDsWaves; ++w) {
+  for (int w = 0; w < kWavesDs; ++w) {
     esl += red_d[0][w];
     esr += red_d[1][w];
   }
@@ -264,18 +300,46 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
   const Excess ex{lb0, log(bk1) - lb0, c0, c1 - c0, static_cast<double>(2 * W + 1)};
   // this wave's range [q0, q1) of the window positions [W, nb - W)
   const int64_t nv = nb - 2 * W > 0 ? nb - 2 * W : 0;
-  const int64_t Lw = (nv + kDsWaves - 1) / kDsWaves;
+  const int64_t Lw = (nv + kWavesDs - 1) / kWavesDs;
   const int64_t q0 = W + wv * Lw;
   const int64_t q1 = (W + (wv + 1) * Lw < nb - W) ? W + (wv + 1) * Lw : nb - W;
   // pass 1: largest excess, first position (per lane, positions increase)
   int64_t be = INT64_MIN, bi = 0;
-  window_walk(counts, dtype, off, q0, q1, W, [&](double S, int64_t i) {
-    const int64_t e = ex(S, i);
-    if (e > be) {
-      be = e;
-      bi = i;
-    }
-  });
+  // window sums of u32 counts stay below 2^53, so they are exact
+  const bool whole = U32 && W < (1 << 20);
+  const uint32_t* cu = static_cast<const uint32_t*>(counts) + off;
+  if (whole) {
+    // The excess as it has to round is evaluated only where a close estimate
+    // (1e-9 of the background is far above its error) leaves it a chance of
+    // exceeding the wave's largest so far: a dozen steps of a wave's range.
+    const double rc = 1.0 / ex.cden;
+    window_walk_u32(cu, q0, q1, W, [&](double S, int64_t i, bool in) {
+      const double bg =
+          ex.wlen * exp_fast(fma(ex.dlb, (static_cast<double>(i) + 0.5 - ex.c0) * rc, ex.lb0));
+      const bool chance = in && !(fma(1e-9, bg, S - bg) < static_cast<double>(be) + 0.25);
+      if (__any(chance)) {
+        // an excess is below 2^53 in size: its double is the integer
+        const double e = chance ? static_cast<double>(ex(S, i)) : -1e19;
+        double m = fmax(e, dpp_row<0x128>(e));
+        m = fmax(m, dpp_row<0x124>(m));
+        m = fmax(m, dpp_row<0x4e>(m));
+        m = fmax(m, dpp_row<0xb1>(m));
+        m = fmax(fmax(readlane_d(m, 0), readlane_d(m, 16)), fmax(readlane_d(m, 32), readlane_d(m, 48)));
+        if (m > static_cast<double>(be)) {
+          be = static_cast<int64_t>(m);
+          bi = i - lane + __builtin_ctzll(__ballot(e == m));
+        }
+      }
+    });
+  } else {
+    window_walk(counts, dtype, off, q0, q1, W, [&](double S, int64_t i) {
+      const int64_t e = ex(S, i);
+      if (e > be) {
+        be = e;
+        bi = i;
+      }
+    });
+  }
   // the largest excess, the first position among equals: over the lanes,
   // then over the waves
 #pragma unroll
@@ -293,7 +357,7 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
   __syncthreads();
   int64_t emax = INT64_MIN, imax = nb / 2;
 #pragma unroll
-  for (int w = 0; w < kDsWaves; ++w)
+  for (int w = 0; w < kWavesDs; ++w)
     if (red_e[w] > emax || (red_e[w] == emax && red_i[w] < imax)) {
       emax = red_e[w];
       imax = red_i[w];
@@ -305,12 +369,46 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
   __syncthreads();
   // pass 2: nearest positions left / right of the peak with 2 e < emax
   int64_t pl = INT64_MIN, pr = INT64_MAX;
-  window_walk(counts, dtype, off, q0, q1, W, [&](double S, int64_t i) {
-    if (i != imax && 2 * ex(S, i) < emax) {
-      if (i < imax) pl = i > pl ? i : pl;  // the largest below the peak
-      else pr = i < pr ? i : pr;           // the smallest above it
+  if (whole) {
+    // outwards from the peak, eight waves on each side, until both are found
+    constexpr int64_t kSide = 64 * (kWavesDs / 2);
+    const bool right = wv < kWavesDs / 2;
+    bool more_l = true, more_r = true;
+    for (int64_t r = 0; more_l || more_r; r += kSide) {
+      const int64_t w0 = right ? imax + 1 + r + 64 * wv : imax - r - 64 * (wv - kWavesDs / 2 + 1);
+      if (right ? more_r : more_l)
+        window_walk_u32(cu, w0 > W ? w0 : W, w0 + 64 < nb - W ? w0 + 64 : nb - W, W,
+                        [&](double S, int64_t i, bool in) {
+                          const uint64_t hit = __ballot(in && 2 * ex(S, i) < emax);
+                          if (!hit) return;
+                          const int64_t base = i - lane;
+                          if (right)
+                            pr = base + __builtin_ctzll(hit);
+                          else
+                            pl = base + 63 - __builtin_clzll(hit);
+                        });
+      if (lane == 0) {
+        red_e[wv] = pl;
+        red_j[wv] = pr;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kWavesDs; ++w) {
+        pl = red_e[w] > pl ? red_e[w] : pl;
+        pr = red_j[w] < pr ? red_j[w] : pr;
+      }
+      more_l = more_l && pl == INT64_MIN && imax - r - kSide > W;
+      more_r = more_r && pr == INT64_MAX && imax + 1 + r + kSide < nb - W;
+      __syncthreads();
     }
-  });
+  } else {
+    window_walk(counts, dtype, off, q0, q1, W, [&](double S, int64_t i) {
+      if (i != imax && 2 * ex(S, i) < emax) {
+        if (i < imax) pl = i > pl ? i : pl;  // the largest below the peak
+        else pr = i < pr ? i : pr;           // the smallest above it
+      }
+    });
+  }
 #pragma unroll
   for (int k = 32; k > 0; k >>= 1) {
     const int64_t ol = __shfl_xor(pl, k), orr = __shfl_xor(pr, k);
@@ -324,7 +422,7 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
   __syncthreads();
   if (t == 0) {
     int64_t l = INT64_MIN, r = INT64_MAX;
-    for (int q = 0; q < kDsWaves; ++q) {
+    for (int q = 0; q < kWavesDs; ++q) {
       l = red_e[q] > l ? red_e[q] : l;
       r = red_j[q] < r ? red_j[q] : r;
     }
@@ -355,8 +453,12 @@ __global__ __launch_bounds__(kDsThreads) void k_default_starts(const void* count
 hipError_t default_starts(int B, const void* counts, int dtype, const int64_t* offsets,
                           const double* ranges, double t_shift, double t_scale, double* theta0,
                           hipStream_t s) {
-  hipLaunchKernelGGL(k_default_starts, dim3(B), dim3(kDsThreads), 0, s, counts, dtype, offsets, ranges,
-                     t_shift, t_scale, theta0);
+  if (dtype == DT_U32)
+    hipLaunchKernelGGL((k_default_starts<512, true>), dim3(B), dim3(512), 0, s, counts, dtype, offsets,
+                       ranges, t_shift, t_scale, theta0);
+  else
+    hipLaunchKernelGGL((k_default_starts<1024, false>), dim3(B), dim3(1024), 0, s, counts, dtype,
+                       offsets, ranges, t_shift, t_scale, theta0);
   return hipGetLastError();
 }
 
