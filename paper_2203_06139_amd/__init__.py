@@ -94,6 +94,7 @@ class HistfitError(RuntimeError):
 _lib = None
 _fast = None   # the native marshalling module, once loaded
 _ctx = {}      # (device, stream handle) -> hf_ctx
+_entered = set()  # keys of _ctx that the native marshalling module knows
 _pool = {}     # device -> contexts created ahead, not yet given to a stream
 _tuning = {}   # device -> (wg_per_cu, cache_bins, block_size) set by fit_set_tuning
 _wave_bins = {}  # device -> wave_bins set by fit_set_wave_bins
@@ -213,7 +214,9 @@ def context(device: int | None = None, stream=None):
     h = _ctx.get(key)
     pool = _pool.setdefault(dev, [])
     if h is not None and len(pool) >= POOL_SIZE:
-        _fast.enter(dev, key[1], h.value)
+        if key not in _entered:
+            _fast.enter(dev, key[1], h.value)
+            _entered.add(key)
         return h
     capturing = torch.cuda.is_current_stream_capturing()
     if h is None:
@@ -228,8 +231,10 @@ def context(device: int | None = None, stream=None):
         while len(pool) < POOL_SIZE:
             pool.append(_new_context(dev))
         _fast.enter(dev, key[1], h.value)
+        _entered.add(key)
     else:
         _fast.leave(dev)
+        _entered.difference_update([k for k in _entered if k[0] == dev])
     return h
 
 
