@@ -165,7 +165,7 @@ __device__ __forceinline__ double clamp_ratio_exponent(double a) {
 // (log_lut_host) and copied into each block's LDS by log_lut_load; the block
 // must synchronise before the first log_lut call.
 __host__ __device__ inline void log_lut_entry(int i, double* ic, double* lnc) {
-  const int j = i ^ (kLogLut / 2);  // top mantissa bits of the arguments with entry i
+  const int j = i ^ (kLogLut / 2 - 1);  // top mantissa bits of the arguments with entry i
   const double c = 1.0 + (j + 0.5) / kLogLut;
   *ic = j >= kLogLut / 2 ? 2.0 * (1.0 / c) : 1.0 / c;
   *lnc = -log(*ic);
@@ -179,15 +179,18 @@ __device__ __forceinline__ void log_lut_load(double2* lut, const double2* __rest
 // FP32-per-bin variant (|f|^4/4 < 1e-14).
 template <bool F32BIN>
 __device__ __forceinline__ double log_lut(double x, const double2* __restrict__ lut) {
-  // x = 2^e m with m in [0.75, 1.5): the high word less that of 0.75 holds e
-  // on top of the table's index.  Six integer operations; with m in [1, 2)
-  // and e corrected for the upper half of the table eight, and 4096 fits of
-  // uneven sizes 946 us instead of 906 with the same bits in every result
+  // x = 2^e m with m in [0.75, 1.5): the high word's distance below that of
+  // 1.5 (in halves, where the difference cannot overflow) holds -e on top of
+  // the table's index.  A negative x, of a bin with a count below zero, gets
+  // ln|x| less 2048 ln 2: a constant per bin.  Six integer operations; with m
+  // in [1, 2) and e corrected for the upper half of the table eight, and 4096
+  // fits of uneven sizes 946 us instead of 906 with the same bits in every
+  // result
   const int hi = __double2hiint(x);
-  const int d = hi - 0x3fe80000;
-  const int e = d >> 20;
-  const double m = __hiloint2double(hi - (d & 0xfff00000), __double2loint(x));
-  const double2 t = lut[(d >> (20 - kLogLutBits)) & (kLogLut - 1)];
+  const int d = 0x1ffbffff - (hi >> 1);
+  const int ne = d >> 19;
+  const double m = __hiloint2double(hi + (ne << 20), __double2loint(x));
+  const double2 t = lut[(d >> (19 - kLogLutBits)) & (kLogLut - 1)];
   const double f = fma(m, t.x, -1.0);
   double p;
   if (F32BIN) {
@@ -203,8 +206,8 @@ __device__ __forceinline__ double log_lut(double x, const double2* __restrict__ 
   // e ln 2 in one rounding: e = 0 for arguments in [0.75, 1.5), where the
   // objective cancels and needs the log to the last bit; elsewhere |ln x| >
   // 0.28 and the term it enters is large, so ~1e-16 relative is ample.
-  const double ed = static_cast<double>(e);
-  return fma(p, f, fma(ed, kLn2, t.y));
+  const double ned = static_cast<double>(ne);
+  return fma(p, f, fma(ned, -kLn2, t.y));
 }
 
 // erf(z / sqrt 2) where phi = exp(-z^2 / 2) is at hand (within a few ulp).
