@@ -314,11 +314,17 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
   const int lane = static_cast<int>(threadIdx.x & 63u);
   const int64_t s0 = steps * wave / waves, s1 = steps * (wave + 1) / waves;
   if (s0 < s1) {
-    double us[G1], ismax = 0.0;
+    // ms: the means for the series' polynomials, no more than 64 widths outside
+    // the histogram: farther away phi is 0 (from 39 on), which only finite
+    // polynomials leave so
+    double us[G1], ms[G1], ismax = 0.0;
+    const double e_lo = E[0], e_hi = E[nb];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       us[g] = gauss_unit(M.is[g], sg[g]);
       ismax = fmax(ismax, fabs(M.is[g]));
+      const double far = 64.0 * fabs(sg[g]);
+      ms[g] = fmin(fmax(M.m[g], e_lo - far), e_hi + far);
     }
     // z, erf and phi at an edge
     struct Edge {
@@ -371,7 +377,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg_edges(NllArgs a) {
         if constexpr (NG > 0) gauss_n(u, e);
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-          const double z = (xc - M.m[g]) * M.is[g], d = 0.5 * h * M.is[g], d2 = d * d;
+          const double z = (xc - ms[g]) * M.is[g], d = 0.5 * h * M.is[g], d2 = d * d;
           double c[kHermMax + 1];
           c[0] = 1.0;
 #pragma unroll
