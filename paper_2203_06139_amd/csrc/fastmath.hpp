@@ -70,8 +70,10 @@ __device__ __forceinline__ double exp_fast(double x) {
 // the order that it is given.
 constexpr double kGaussU = 8.49321800288019068681e-01;     // sqrt(log2(e) / 2)
 constexpr double kGaussULo = -2.59594641045974034667e-17;  // and its remainder
-constexpr double kGaussUInv = 1.17741002251547466351e+00;
-constexpr double kGaussUInv2 = 1.38629436111989057245e+00;
+constexpr double kGaussUInv2 = 1.38629436111989057245e+00;    // kGaussU^-2
+constexpr double kGaussUInv2Lo = 4.63809362769259911684e-17;
+constexpr double kGaussUInv3 = 1.63223687493924596303e+00;    // kGaussU^-3
+constexpr double kGaussUInv3Lo = 5.25745411534361271364e-17;
 
 // kGaussU / s to the last bit, from is = 1 / s.
 __device__ __forceinline__ double gauss_unit(double is, double s) {

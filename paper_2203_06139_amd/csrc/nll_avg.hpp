@@ -600,10 +600,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_edges(NllArgs a) {
     }
   }
   __shared__ double fac[NV];
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) fac[k] = gauss_factor(M, k);
-  }
+  if (threadIdx.x < NV) fac[threadIdx.x] = gauss_factor(M, us, threadIdx.x);
   publish_objective<NV>(a, acc, flags | (finite ? 0 : ST_NONFINITE), fac, output_seed(a));
 }
 

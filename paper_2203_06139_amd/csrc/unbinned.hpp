@@ -246,16 +246,11 @@ __global__ __launch_bounds__(kBlock, kUbWaves<NG>) void k_nll_unbinned(UnbinnedA
   constexpr int NV = GRAD ? S::P + 1 : 1;
   __shared__ double2 lut[kLogLut];
   __shared__ double lamd[S::P + 1];
-  __shared__ double ff[S::P + 1];
   log_lut_load(lut, a.log_lut);
   Model1D<NG, BKG> M;
   M.init(a.theta, a.t_shift, a.t_scale);
   const bool finite = all_finite(a.theta, S::P);
-  if (threadIdx.x == 0) {
-    if (blockIdx.x == 0) lambda_terms<NG, BKG>(a, M, lamd);
-#pragma unroll
-    for (int k = 0; k <= S::P; ++k) ff[k] = gauss_factor(M, k);
-  }
+  if (threadIdx.x == 0 && blockIdx.x == 0) lambda_terms<NG, BKG>(a, M, lamd);
   __syncthreads();
   double us[NG > 0 ? NG : 1];
 #pragma unroll
@@ -333,7 +328,7 @@ __global__ __launch_bounds__(kBlock, kUbWaves<NG>) void k_nll_unbinned(UnbinnedA
   // L = Lambda - sum w ln lambda: every block publishes -(its sums) times
   // the final factors, and block 0 adds Lambda and its derivatives
   __shared__ double fac[NV];
-  if (threadIdx.x < NV) fac[threadIdx.x] = -ff[threadIdx.x];
+  if (threadIdx.x < NV) fac[threadIdx.x] = -gauss_factor(M, us, threadIdx.x);
   grid_publish<NV>(acc, flags | (finite ? 0 : ST_NONFINITE), fac, lamd, a.part, a.part_flags,
                    [&](int k, double x, int f) {
                      write_output({a.nll_out, a.grad_out, a.status_out, 0u}, k, x, f, 1.0);
