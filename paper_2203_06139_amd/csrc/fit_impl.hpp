@@ -308,8 +308,12 @@ __device__ __forceinline__ int run_groups(int64_t nb, int threads) {
 }
 
 // The same evaluation in FP64 by runs of S groups of four bins (run_1d), in
-// single groups where a run is too long for the recurrences, and bin by bin
-// where four bins are.  Bound: VALU issue, about 43 instructions per bin.
+// single groups where a run is too long for the recurrences, and in groups
+// with an exponential per bin and Gaussian where four bins are.
+// Bound: VALU issue, about 43 instructions per bin in runs.  Narrow peaks (1 to
+// 3 bins): the four bins' chains side by side, 10,000 bins of one Gaussian and
+// a line 71 us a fit, bin by bin 123; 64 of three Gaussians on 100,000 bins
+// 1.55 ms and 2.7.
 // Against four-bin chunks, each with its own exps and expansion, and counts
 // read as they were needed: one evaluation and iteration of a 65,536-bin
 // Gauss + exponential histogram on 256 threads 67.5 -> 32 us; 4096 such
@@ -330,23 +334,34 @@ __device__ __forceinline__ void wg_eval_runs(const FitArgs& a, FitShared<NG, BKG
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = 0.0;
   int flags = 0;
-  const int nq = run_quads(nb);
-  if (M.recur && nq > 0) {
-    auto runs = [&](auto kind) {
-      RunCounts<decltype(kind)::value> next(src, tid, nq, S, BLK);
+  // with a bin per thread at most, a group of four would leave threads idle
+  // (256 narrow bins on 256 threads: 27 us a fit, in groups 29)
+  const int nq = M.recur || nb > BLK ? run_quads(nb) : 0;
+  auto sweep = [&](auto kind) {
+    RunCounts<decltype(kind)::value> next(src, tid, nq, S, BLK);
+    if (M.recur) {
       for (int q = tid * S; q < nq; q += BLK * S)
         run_1d<NG, BKG, OBJ, GRAD>(M, lut, fma(4.0 * q, hx, x0), nq - q < S ? nq - q : S, next, acc,
                                    flags);
-    };
+    } else {
+      const double w4[4] = {1.0, 1.0, 1.0, 1.0};
+      for (int q = tid; q < nq; q += BLK) {
+        double n4[4], l4[4];
+        next(n4);
+        chunk_1d<NG, BKG, OBJ, GRAD, false, false>(M, lut, fma(4.0 * q, hx, x0), n4, w4, acc, flags, l4);
+      }
+    }
+  };
+  if (nq > 0) {
     if (src.lds)
-      runs(std::integral_constant<int, SRC_LDS>{});
+      sweep(std::integral_constant<int, SRC_LDS>{});
     else if (src.dtype == DT_U32)
-      runs(std::integral_constant<int, SRC_U32>{});
+      sweep(std::integral_constant<int, SRC_U32>{});
     else
-      runs(std::integral_constant<int, SRC_ANY>{});
+      sweep(std::integral_constant<int, SRC_ANY>{});
   }
   const double w1[1] = {1.0};
-  for (int64_t i = (M.recur ? 4 * static_cast<int64_t>(nq) : 0) + tid; i < nb; i += BLK) {
+  for (int64_t i = 4 * static_cast<int64_t>(nq) + tid; i < nb; i += BLK) {
     const double n1[1] = {src.at(i)};
     double l1[1];
     chunk_1d<NG, BKG, OBJ, GRAD, false, false>(M, lut, fma(static_cast<double>(i), hx, x0), n1, w1,
