@@ -204,7 +204,7 @@ __device__ __forceinline__ void window_walk(const void* counts, int dtype, int64
 
 // The same sums for u32 counts, which are integers: exact in any order, so the
 // prefix goes by DPP, and the next step's counts are requested ahead.  fn(S, i,
-// in) is called by the whole wave.
+// in) is called by the whole wave, whose walk ends where it returns true.
 __device__ __forceinline__ double wave_prefix(double d) {
   const int row = static_cast<int>(threadIdx.x & 63u) >> 4;
   d += dpp_row<0x111>(d);  // row_shr:1, 2, 4, 8
@@ -221,6 +221,7 @@ __device__ __forceinline__ void window_walk_u32(const uint32_t* __restrict__ c, 
   if (q0 >= q1) return;
   const int lane = static_cast<int>(threadIdx.x & 63u);
   double s0 = 0.0;
+#pragma unroll 4
   for (int64_t q = q0 - W + lane; q <= q0 + W; q += 64) s0 += c[q];
   double carry = wave_sum(s0);  // S(q0), then S of the previous step's last position
   auto step = [&](int64_t i) {  // S(i) - S(i - 1)
@@ -231,7 +232,7 @@ __device__ __forceinline__ void window_walk_u32(const uint32_t* __restrict__ c, 
     const int64_t i = base + lane;
     const double S = carry + wave_prefix(next);
     next = step(i + 64);
-    fn(S, i, i < q1);
+    if (fn(S, i, i < q1)) return;
     carry = readlane_d(S, 63);
   }
 }
@@ -242,8 +243,12 @@ __device__ __forceinline__ void window_walk_u32(const uint32_t* __restrict__ c, 
 // segment of positions with scattered loads, 0.88 ms with 16 waves and every
 // excess (an exp and a division) rounded as the direct evaluation does, twice;
 // 0.47 ms with the excess only where an estimate leaves it a chance, and the
-// width searched outwards from the peak.  4096 of 10,000 bins 537 -> 275 us,
-// 1024 of 64..512 54.9 -> 29.0.  With 1024 threads one block fits a CU (670,
+// width searched outwards from the peak.  In us, walked twice and now: 4096 of
+// 64..512 bins 182 and 71, 4096 of 10,000 516 and 256, 64 of 65,536 153 and 105;
+// one of 1e6 with a peak of 2% of the range 2144 and 1236, of 10% 2142 and
+// 1706, without a peak 2105 and 2135 (the search then covers all of it).  (With
+// 1 to 6% more time per position, before the loops' constants were
+// materialised in them:) with 1024 threads one block fits a CU (670,
 // 458, 66.7), with spills two (884, 581, 79.2); 256 threads take 476, 231 and
 // 22.2, but 251 us instead of 160 for 64 histograms of 65,536.
 template <int T, bool U32>
@@ -308,14 +313,16 @@ __global__ __launch_bounds__(T, 4) void k_default_starts(const void* counts, int
   // window sums of u32 counts stay below 2^53, so they are exact
   const bool whole = U32 && W < (1 << 20);
   const uint32_t* cu = static_cast<const uint32_t*>(counts) + off;
+  const double rc = 1.0 / ex.cden;
+  auto background = [&](int64_t i) {  // of the window, to 1e-9 and far better
+    return ex.wlen * exp_fast(fma(ex.dlb, (static_cast<double>(i) + 0.5 - ex.c0) * rc, ex.lb0));
+  };
   if (whole) {
     // The excess as it has to round is evaluated only where a close estimate
     // (1e-9 of the background is far above its error) leaves it a chance of
     // exceeding the wave's largest so far: a dozen steps of a wave's range.
-    const double rc = 1.0 / ex.cden;
     window_walk_u32(cu, q0, q1, W, [&](double S, int64_t i, bool in) {
-      const double bg =
-          ex.wlen * exp_fast(fma(ex.dlb, (static_cast<double>(i) + 0.5 - ex.c0) * rc, ex.lb0));
+      const double bg = background(i);
       const bool chance = in && !(fma(1e-9, bg, S - bg) < static_cast<double>(be) + 0.25);
       if (__any(chance)) {
         // an excess is below 2^53 in size: its double is the integer
@@ -330,6 +337,7 @@ __global__ __launch_bounds__(T, 4) void k_default_starts(const void* counts, int
           bi = i - lane + __builtin_ctzll(__ballot(e == m));
         }
       }
+      return false;
     });
   } else {
     window_walk(counts, dtype, off, q0, q1, W, [&](double S, int64_t i) {
@@ -370,26 +378,42 @@ __global__ __launch_bounds__(T, 4) void k_default_starts(const void* counts, int
   // pass 2: nearest positions left / right of the peak with 2 e < emax
   int64_t pl = INT64_MIN, pr = INT64_MAX;
   if (whole) {
-    // outwards from the peak, eight waves on each side, until both are found
-    constexpr int64_t kSide = 64 * (kWavesDs / 2);
-    const bool right = wv < kWavesDs / 2;
-    bool more_l = true, more_r = true;
-    for (int64_t r = 0; more_l || more_r; r += kSide) {
-      const int64_t w0 = right ? imax + 1 + r + 64 * wv : imax - r - 64 * (wv - kWavesDs / 2 + 1);
-      if (right ? more_r : more_l)
-        window_walk_u32(cu, w0 > W ? w0 : W, w0 + 64 < nb - W ? w0 + 64 : nb - W, W,
-                        [&](double S, int64_t i, bool in) {
-                          const uint64_t hit = __ballot(in && 2 * ex(S, i) < emax);
-                          if (!hit) return;
-                          const int64_t base = i - lane;
-                          if (right)
-                            pr = base + __builtin_ctzll(hit);
-                          else
-                            pl = base + 63 - __builtin_clzll(hit);
-                        });
+    // Outwards from the peak until both are found: half of the waves on each
+    // side, all of them on the side that is left.  A wave takes a stretch of L
+    // positions per round, a window's length (four where one side is left, which
+    // is then long), so that the window sum it starts from costs no more than
+    // the walk, and a search of n positions reads less than 3 n counts; the
+    // excess is evaluated as in pass 1, where an estimate leaves it a chance to
+    // be below half of the peak's.
+    const int64_t L0 = (2 * W + 64) / 64 * 64;
+    const double below = static_cast<double>((emax - 1) >> 1) + 0.75;
+    int64_t dl = 0, dr = 0;  // positions searched on each side
+    bool more_l = imax > W, more_r = imax + 1 < nb - W;
+    while (more_l || more_r) {
+      const int64_t L = more_l && more_r ? L0 : 4 * L0;
+      const int nr = !more_r ? 0 : (more_l ? kWavesDs / 2 : kWavesDs);
+      const bool right = wv < nr;
+      const int64_t w0 = right ? imax + 1 + dr + L * wv : imax - dl - L * (wv - nr + 1);
+      int64_t fl = INT64_MIN, fr = INT64_MAX;
+      window_walk_u32(cu, w0 > W ? w0 : W, w0 + L < nb - W ? w0 + L : nb - W, W,
+                      [&](double S, int64_t i, bool in) {
+                        bool chance = in;
+                        if (dl + dr > 0) {  // in the first round most have one
+                          const double bg = background(i);
+                          chance = in && fma(-1e-9, bg, S - bg) < below;
+                          if (!__any(chance)) return false;
+                        }
+                        const uint64_t hit = __ballot(chance && 2 * ex(S, i) < emax);
+                        if (!hit) return false;
+                        if (right)
+                          fr = i - lane + __builtin_ctzll(hit);  // the first
+                        else
+                          fl = i - lane + 63 - __builtin_clzll(hit);  // the last so far
+                        return right;
+                      });
       if (lane == 0) {
-        red_e[wv] = pl;
-        red_j[wv] = pr;
+        red_e[wv] = fl;
+        red_j[wv] = fr;
       }
       __syncthreads();
 #pragma unroll
@@ -397,8 +421,10 @@ __global__ __launch_bounds__(T, 4) void k_default_starts(const void* counts, int
         pl = red_e[w] > pl ? red_e[w] : pl;
         pr = red_j[w] < pr ? red_j[w] : pr;
       }
-      more_l = more_l && pl == INT64_MIN && imax - r - kSide > W;
-      more_r = more_r && pr == INT64_MAX && imax + 1 + r + kSide < nb - W;
+      dr += nr * L;
+      dl += (kWavesDs - nr) * L;
+      more_l = more_l && pl == INT64_MIN && imax - dl > W;
+      more_r = more_r && pr == INT64_MAX && imax + 1 + dr < nb - W;
       __syncthreads();
     }
   } else {
