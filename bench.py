@@ -950,7 +950,7 @@ def bench_smallfits(args, hf, datagen, np, torch, dev):
     th[:, 2] *= 1 + 0.05 * rng.standard_normal(B)
     th[:, 3] += 0.05 * rng.standard_normal(B)
     near = modes(torch.as_tensor(th, device=dev), 1024)
-    hf.fit_set_wave_bins(0)
+    hf.fit_set_wave_bins(hf.WAVE_AUTO)
     t = res["waves"]
     print(json.dumps(dict(
         metric="fits/s at |dNLL|<1e-6", value=t["fits_per_s"], unit="fits/s", n_gpus=1,

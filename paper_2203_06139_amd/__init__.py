@@ -33,6 +33,7 @@ ST_DOMAIN, ST_NONFINITE = 1, 2
 FIT_CONVERGED, FIT_MAXITER, FIT_LSFAIL, FIT_NONFINITE, FIT_DOMAIN, FIT_BADHIST = range(6)
 IDENTITY, FISHER = 0, 1  # fit_batch hessian_init
 ADJOINT, FINITE_DIFF = 0, 1  # fit_batch gradient
+WAVE_AUTO = 0x7fffffff  # fit_set_wave_bins: the library chooses by the batch
 
 
 class HfModel(ctypes.Structure):
@@ -645,7 +646,8 @@ def fit_set_tuning(wg_per_cu: int, cache_bins: int, block_size: int = 256, devic
 
 def fit_set_wave_bins(wave_bins: int, device=None):
     """One wave per histogram of at most wave_bins bins in fit_batch (see
-    hf_fit_set_wave_bins; 0 turns it off) on every context of the device."""
+    hf_fit_set_wave_bins; 0 turns it off, WAVE_AUTO, the setting before the
+    first call, lets the library choose) on every context of the device."""
     import torch
     dev = torch.cuda.current_device() if device is None else int(device)
     ctx = context(dev)
@@ -658,6 +660,7 @@ def fit_set_wave_bins(wave_bins: int, device=None):
 
 
 def fit_get_wave_bins(device=None) -> int:
+    """The setting, as fit_set_wave_bins takes it back."""
     return int(load().hf_fit_get_wave_bins(context(device)))
 
 

@@ -748,7 +748,7 @@ HF_EXPORT int fit_batch(hf_ctx* c, int32_t B, const void* counts, int32_t dtype,
       return fail(c, HF_EINVAL, "LDS cache of %d bins exceeds the %d this fit kernel can hold",
                   c->fit.cache_bins, cap);
   }
-  if (c->fit.wave_bins > 0) {
+  if (c->fit.wave_bins > 0 && c->fit.wave_bins != HF_WAVE_AUTO) {
     const int cap = hf::fit_max_wave_bins(m->n_gauss, bkg_code(m), obj, c->fit.block);
     if (c->fit.wave_bins > cap)
       return fail(c, HF_EINVAL, "wave_bins %d exceeds the %d this model's waves can hold in LDS",
@@ -931,6 +931,8 @@ HF_EXPORT int hf_fit_set_tuning(hf_ctx* c, int32_t wg_per_cu, int32_t cache_bins
   return HF_OK;
 }
 
+static_assert(hf::kWaveAuto == HF_WAVE_AUTO, "the header's value");
+
 HF_EXPORT int hf_fit_set_wave_bins(hf_ctx* c, int32_t wave_bins) {
   if (!c) return HF_EINVAL;
   if (wave_bins < 0) return fail(c, HF_EINVAL, "wave_bins must be >= 0");
@@ -939,7 +941,7 @@ HF_EXPORT int hf_fit_set_wave_bins(hf_ctx* c, int32_t wave_bins) {
 }
 
 HF_EXPORT int hf_fit_get_wave_bins(const hf_ctx* c) {
-  return c ? std::max(c->fit.wave_bins, 0) : HF_EINVAL;
+  return c ? c->fit.wave_bins : HF_EINVAL;
 }
 
 HF_EXPORT int hf_fit_max_wave_bins(hf_ctx* c, const hf_model* m, int32_t objective,

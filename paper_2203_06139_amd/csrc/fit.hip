@@ -138,7 +138,7 @@ int fit_max_wave_bins(int n_gauss, int bkg, int obj, int block) {
   return m > 0 ? m : 0;
 }
 
-// wave_bins of a context on which none was set.  One wave per histogram saves
+// wave_bins of a context set to HF_WAVE_AUTO.  One wave per histogram saves
 // the workgroup barriers and gives a CU eight fits at once, but each of these
 // fits takes longer, which shows when there are few: so for batches of at
 // least two histograms per workgroup, and up to 2048 bins, where the slots of
@@ -159,7 +159,7 @@ hipError_t launch_fit(int n_gauss, int bkg, FitArgs a, int num_cu, FitScratch* s
   int grid = num_cu * s->wg_per_cu;
   if (grid > a.B) grid = a.B;
   a.cache_bins = s->cache_bins;
-  a.wave_bins = s->wave_bins >= 0 ? s->wave_bins : auto_wave_bins(n_gauss, bkg, a, grid, s);
+  a.wave_bins = s->wave_bins != kWaveAuto ? s->wave_bins : auto_wave_bins(n_gauss, bkg, a, grid, s);
   // batches above kMaxRankB run in index order, and so do those of which
   // every workgroup takes one (the order could change nothing)
   a.sorted = (a.B <= kMaxRankB && a.B <= s->cap && (grid < a.B || a.wave_bins > 0)) ? 1 : 0;

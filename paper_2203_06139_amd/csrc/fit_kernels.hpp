@@ -45,6 +45,8 @@ struct FitArgs {
   int32_t wave_bins;       // histograms of at most this many bins are fitted one per wave (0: off)
 };
 
+constexpr int kWaveAuto = 0x7fffffff;  // HF_WAVE_AUTO: chosen by the batch
+
 // Device scratch of the fitter, owned by the context.  `order` grows with B;
 // the two counters are cleared once at creation and re-armed by the kernel.
 struct FitScratch {
@@ -54,7 +56,7 @@ struct FitScratch {
   int wg_per_cu = 2;   // persistent workgroups per CU
   int cache_bins = 0;  // histograms with at most this many u32 bins live in LDS
   int block = 256;     // threads per workgroup (256 or 512)
-  int wave_bins = -1;  // one wave per histogram of at most this many bins (0: off, -1: by batch)
+  int wave_bins = kWaveAuto;  // one wave per histogram of at most this many bins (0: off)
 };
 
 hipError_t fit_scratch_init(FitScratch* s);
