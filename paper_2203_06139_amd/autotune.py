@@ -6,8 +6,9 @@ timing fit_batch (HIP events) on a sample of the batch to be fitted (the
 whole batch when `sample` is at least its size), keeps the fastest
 configuration whose fits agree with the FP64 fit of the same sample
 (|dNLL| < 1e-6 where both converge), then on that shape the size below which
-every wave fits a histogram of its own (wave_bins: off, 256 .. 2048 bins),
-applies the result to the device's contexts, and caches it as JSON keyed by
+every wave fits a histogram of its own (wave_bins: off, the library's choice by
+the batch, 256 .. 2048 bins; on a larger sample where the batch is large enough
+for that choice), applies the result to the device's contexts, and caches it as JSON keyed by
 (GPU arch, CU count, model, objective, precision).
 When no configuration agrees, the shape in place before the search is
 restored and RuntimeError is raised.  Cache file: $HF_AUTOTUNE_CACHE or
@@ -21,7 +22,7 @@ import os
 
 import torch
 
-from . import (FP32_BIN, FP64, POISSON, Model, fit_batch, fit_get_tuning, fit_get_wave_bins,
+from . import (FP32_BIN, FP64, POISSON, WAVE_AUTO, Model, fit_batch, fit_get_tuning, fit_get_wave_bins,
                fit_max_cache_bins, fit_max_wave_bins, fit_set_tuning, fit_set_wave_bins)
 
 BLOCKS = (256, 512)
@@ -48,6 +49,13 @@ def key(model: Model, objective: int, precision: int) -> str:
                                                   p.multi_processor_count, model.kind,
                                                   model.n_gauss, model.poly_degree, objective,
                                                   precision)
+
+
+def _workgroups(counts, wg_per_cu: int):
+    """Workgroups of a full launch, None for counts that are not on a GPU."""
+    if not counts.is_cuda:
+        return None
+    return wg_per_cu * torch.cuda.get_device_properties(counts.device).multi_processor_count
 
 
 def _time(fn, reps=2):
@@ -82,10 +90,16 @@ def tune_fit(counts, offsets, ranges, model: Model, theta0, objective=POISSON, p
     fit_set_wave_bins(0)
     B = offsets.numel() - 1
     g = torch.Generator().manual_seed(seed)
-    idx = torch.randperm(B, generator=g)[:min(sample, B)].sort().values
-    fs = subset(FitSet(counts, offsets.to(counts.device), ranges.to(counts.device)), idx.to(counts.device))
-    th0 = theta0.to(counts.device)[idx.to(counts.device)].contiguous()
-    ref = fit_batch(fs.counts, fs.offsets, fs.ranges, model, th0, objective=objective, precision=FP64)
+
+    def draw(n):
+        idx = torch.randperm(B, generator=g)[:min(n, B)].sort().values.to(counts.device)
+        fs = subset(FitSet(counts, offsets.to(counts.device), ranges.to(counts.device)), idx)
+        th0 = theta0.to(counts.device)[idx].contiguous()
+        ref = fit_batch(fs.counts, fs.offsets, fs.ranges, model, th0, objective=objective,
+                        precision=FP64)
+        return fs, th0, ref
+
+    fs, th0, ref = draw(sample)
     polishes = POLISH if precision == FP32_BIN else (0.0,)
     space = []
     for blk in BLOCKS:
@@ -113,12 +127,21 @@ def tune_fit(counts, offsets, ranges, model: Model, theta0, objective=POISSON, p
                            "the previous shape %r is kept" % (before,))
     best = dict(min(ok, key=lambda r: r["ms"]), wave_bins=0)
     fit_set_tuning(best["wg_per_cu"], best["cache_bins"], best["block_size"])
-    # second stage, on the chosen shape: one wave per histogram below wave_bins
+    # second stage, on the chosen shape: one wave per histogram below wave_bins.
+    # The library chooses it for batches of at least two histograms per
+    # workgroup, so a batch of that many is timed with a sample of that many.
     capw = fit_max_wave_bins(model, objective, best["block_size"])
     run = lambda: fit_batch(fs.counts, fs.offsets, fs.ranges, model, th0, objective=objective,
                             precision=precision, polish_edm=best["polish_edm"])
-    for wb in WAVE_BINS:
-        if wb > capw:
+    groups = _workgroups(counts, best["wg_per_cu"])
+    sizes = WAVE_BINS
+    if groups is not None and B >= 2 * groups:
+        sizes = (WAVE_AUTO,) + WAVE_BINS
+        if fs.offsets.numel() - 1 < 2 * groups:
+            fs, th0, ref = draw(2 * groups)
+            best["ms"] = _time(run)
+    for wb in sizes:
+        if wb > capw and wb != WAVE_AUTO:
             continue
         fit_set_wave_bins(wb)
         ms = _time(run)
