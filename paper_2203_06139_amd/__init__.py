@@ -95,7 +95,6 @@ class HistfitError(RuntimeError):
 _lib = None
 _fast = None   # the native marshalling module, once loaded
 _ctx = {}      # (device, stream handle) -> hf_ctx
-_entered = set()  # keys of _ctx that the native marshalling module knows
 _pool = {}     # device -> contexts created ahead, not yet given to a stream
 _tuning = {}   # device -> (wg_per_cu, cache_bins, block_size) set by fit_set_tuning
 _wave_bins = {}  # device -> wave_bins set by fit_set_wave_bins
@@ -169,7 +168,7 @@ def load():
                L.hf_fit_get_tuning, L.hf_fit_max_cache_bins, L.hf_fit_set_wave_bins,
                L.hf_fit_get_wave_bins, L.hf_fit_max_wave_bins):
         fn.restype = ctypes.c_int
-    _fastcall.init(L._handle)
+    _fastcall.init(L._handle, _ctx, _pool, POOL_SIZE)
     _fast = _fastcall
     _lib = L
     return L
@@ -200,10 +199,8 @@ def context(device: int | None = None, stream=None):
     which a stream being captured into a graph must not do, so calls outside
     capture keep POOL_SIZE spare contexts ready, and a stream first seen
     during capture takes one of them.  `stream` defaults to the device's
-    current torch stream.  A context is entered into the native marshalling
-    module while the spare contexts are complete; the native calls do not come
-    through here, so they are all taken out again when a capture takes a spare
-    one, and the next call outside capture makes it up."""
+    current torch stream.  The native calls look _ctx and _pool up themselves
+    and come through here only where something has to be made."""
     import torch
     load()
     if not torch.cuda.is_available():
@@ -215,9 +212,6 @@ def context(device: int | None = None, stream=None):
     h = _ctx.get(key)
     pool = _pool.setdefault(dev, [])
     if h is not None and len(pool) >= POOL_SIZE:
-        if key not in _entered:
-            _fast.enter(dev, key[1], h.value)
-            _entered.add(key)
         return h
     capturing = torch.cuda.is_current_stream_capturing()
     if h is None:
@@ -231,11 +225,6 @@ def context(device: int | None = None, stream=None):
     if not capturing:
         while len(pool) < POOL_SIZE:
             pool.append(_new_context(dev))
-        _fast.enter(dev, key[1], h.value)
-        _entered.add(key)
-    else:
-        _fast.leave(dev)
-        _entered.difference_update([k for k in _entered if k[0] == dev])
     return h
 
 

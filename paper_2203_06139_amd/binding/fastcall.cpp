@@ -24,7 +24,6 @@
 #include <dlfcn.h>
 #include <torch/csrc/autograd/python_variable.h>
 
-#include <map>
 #include <optional>
 
 #include "../../include/histfit.h"
@@ -41,11 +40,15 @@ struct Api {
   decltype(&::fit_batch) fit = nullptr;
 } api;
 
-// Contexts of (device, stream) pairs, entered by the Python side.
-std::map<std::pair<int, intptr_t>, hf_ctx*> contexts;
+// The Python side's dictionaries: (device, stream) -> context, device -> list of
+// spare contexts, of which a call outside capture keeps `spares`.  They are
+// looked up on every call, so that there is one record of the contexts.
+PyObject* contexts = nullptr;
+PyObject* pools = nullptr;
+Py_ssize_t spares = 0;
 
 PyObject *s_counts, *s_weights, *s_edges, *s_xrange, *s_yrange, *s_kind, *s_n_gauss, *s_poly_degree,
-    *s_t_shift, *s_t_scale, *s_bin_average;
+    *s_t_shift, *s_t_scale, *s_bin_average, *s_value;
 
 struct Owned {  // a new reference
   PyObject* o;
@@ -196,12 +199,19 @@ struct Hist {
   }
 };
 
-// The current stream of the device and its context.
+// The current stream of the device and its context, null where context() in the
+// Python code has something to do (no context yet, spares to make up).
 hf_ctx* context_of(int dev, hf_stream_t* stream) {
   const hipStream_t s = c10::hip::getCurrentHIPStream(static_cast<c10::DeviceIndex>(dev)).stream();
   *stream = reinterpret_cast<hf_stream_t>(s);
-  const auto it = contexts.find({dev, reinterpret_cast<intptr_t>(s)});
-  return it == contexts.end() ? nullptr : it->second;
+  Owned d(PyLong_FromLong(dev)), h(PyLong_FromVoidPtr(s));
+  if (!d.o || !h.o) return nullptr;
+  PyObject* pool = PyDict_GetItemWithError(pools, d.o);
+  if (!pool || !PyList_Check(pool) || PyList_GET_SIZE(pool) < spares) return nullptr;
+  Owned key(PyTuple_Pack(2, d.o, h.o));
+  PyObject* c = key.o ? PyDict_GetItemWithError(contexts, key.o) : nullptr;
+  Owned value(c ? PyObject_GetAttr(c, s_value) : nullptr);  // of a ctypes.c_void_p
+  return value.o && PyLong_Check(value.o) ? static_cast<hf_ctx*>(PyLong_AsVoidPtr(value.o)) : nullptr;
 }
 
 // Runs f (a call of the library) without the interpreter lock.
@@ -473,8 +483,11 @@ PyObject* fast_fit(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// (handle of libhistfit.so)
-PyObject* init_api(PyObject*, PyObject* handle) {
+// (handle of libhistfit.so, contexts, pools, spares)
+PyObject* init_api(PyObject*, PyObject* args) {
+  PyObject *handle, *ctx, *pool;
+  Py_ssize_t n;
+  if (!PyArg_ParseTuple(args, "OO!O!n", &handle, &PyDict_Type, &ctx, &PyDict_Type, &pool, &n)) return nullptr;
   void* h = PyLong_AsVoidPtr(handle);
   if (!h) return nullptr;
   Api f;
@@ -489,28 +502,12 @@ PyObject* init_api(PyObject*, PyObject* handle) {
     PyErr_SetString(PyExc_RuntimeError, "libhistfit.so lacks an entry point");
     return nullptr;
   }
+  Py_INCREF(ctx);
+  Py_INCREF(pool);
+  Py_XSETREF(contexts, ctx);
+  Py_XSETREF(pools, pool);
+  spares = n;
   api = f;
-  Py_RETURN_NONE;
-}
-
-// (device, stream, context): the context to use on that stream
-PyObject* enter(PyObject*, PyObject* args) {
-  int dev;
-  PyObject *stream, *ctx;
-  if (!PyArg_ParseTuple(args, "iOO", &dev, &stream, &ctx)) return nullptr;
-  const intptr_t s = static_cast<intptr_t>(PyLong_AsSsize_t(stream));
-  void* c = PyLong_AsVoidPtr(ctx);
-  if (PyErr_Occurred()) return nullptr;
-  contexts[{dev, s}] = static_cast<hf_ctx*>(c);
-  Py_RETURN_NONE;
-}
-
-// (device): forget the contexts of that device's streams
-PyObject* leave(PyObject*, PyObject* device) {
-  const long dev = PyLong_AsLong(device);
-  if (dev == -1 && PyErr_Occurred()) return nullptr;
-  for (auto it = contexts.begin(); it != contexts.end();)
-    it = it->first.first == dev ? contexts.erase(it) : std::next(it);
   Py_RETURN_NONE;
 }
 
@@ -522,9 +519,7 @@ PyMethodDef methods[] = {
     {"fisher_covariance", FAST(fast_covariance), nullptr},
     {"nll_unbinned", FAST(fast_unbinned), nullptr},
     {"fit_batch", FAST(fast_fit), nullptr},
-    {"init", init_api, METH_O, nullptr},
-    {"enter", enter, METH_VARARGS, nullptr},
-    {"leave", leave, METH_O, nullptr},
+    {"init", init_api, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods,
@@ -539,7 +534,8 @@ PyMODINIT_FUNC PyInit__fastcall() {
   } names[] = {{&s_counts, "counts"},     {&s_weights, "weights"}, {&s_edges, "edges"},
                {&s_xrange, "xrange"},     {&s_yrange, "yrange"},   {&s_kind, "kind"},
                {&s_n_gauss, "n_gauss"},   {&s_poly_degree, "poly_degree"},
-               {&s_t_shift, "t_shift"},   {&s_t_scale, "t_scale"}, {&s_bin_average, "bin_average"}};
+               {&s_t_shift, "t_shift"},   {&s_t_scale, "t_scale"}, {&s_bin_average, "bin_average"},
+               {&s_value, "value"}};
   for (auto& n : names)
     if (!(*n.p = PyUnicode_InternFromString(n.s))) return nullptr;
   return PyModule_Create(&module);
