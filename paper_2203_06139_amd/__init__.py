@@ -168,7 +168,7 @@ def load():
                L.hf_fit_get_tuning, L.hf_fit_max_cache_bins, L.hf_fit_set_wave_bins,
                L.hf_fit_get_wave_bins, L.hf_fit_max_wave_bins):
         fn.restype = ctypes.c_int
-    _fastcall.init(L._handle, _ctx, _pool, POOL_SIZE)
+    _fastcall.init(L._handle, _ctx, _pool, POOL_SIZE, HistfitError)
     _fast = _fastcall
     _lib = L
     return L

@@ -11,10 +11,11 @@
 // Each function here takes the Python function's arguments, and where every
 // tensor already is what the kernels need (plain tensors on one GPU, dtypes,
 // contiguity, sizes) and the stream's context is known, it allocates the
-// outputs, makes the C call and returns the Python function's result.  In
+// outputs, makes the C call and returns the Python function's result, or
+// raises HistfitError with the library's message where the call fails.  In
 // every other case (conversions, a first call on a stream, wrong arguments,
-// an error of the call, active dispatch modes) it returns None and does
-// nothing, and the Python code after it converts or raises.
+// active dispatch modes) it returns None and does nothing, and the Python code
+// after it converts or raises.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -38,7 +39,9 @@ struct Api {
   decltype(&::hf_nll_fisher) fisher = nullptr;
   decltype(&::hf_fisher_covariance) covariance = nullptr;
   decltype(&::fit_batch) fit = nullptr;
+  decltype(&::hf_last_error) last_error = nullptr;
 } api;
+PyObject* error_type = nullptr;  // HistfitError
 
 // The Python side's dictionaries: (device, stream) -> context, device -> list of
 // spare contexts, of which a call outside capture keeps `spares`.  They are
@@ -204,38 +207,71 @@ struct Hist {
 hf_ctx* context_of(int dev, hf_stream_t* stream) {
   const hipStream_t s = c10::hip::getCurrentHIPStream(static_cast<c10::DeviceIndex>(dev)).stream();
   *stream = reinterpret_cast<hf_stream_t>(s);
-  Owned d(PyLong_FromLong(dev)), h(PyLong_FromVoidPtr(s));
-  if (!d.o || !h.o) return nullptr;
-  PyObject* pool = PyDict_GetItemWithError(pools, d.o);
+  // the key's objects, kept while calls stay on one stream
+  static struct {
+    int dev = -1;
+    hipStream_t s = nullptr;
+    PyObject* key = nullptr;
+  } last;
+  if (last.dev != dev || last.s != s || !last.key) {
+    PyObject* k = Py_BuildValue("iN", dev, PyLong_FromVoidPtr(s));
+    if (!k) return nullptr;
+    Py_XSETREF(last.key, k);
+    last.dev = dev;
+    last.s = s;
+  }
+  PyObject* pool = PyDict_GetItemWithError(pools, PyTuple_GET_ITEM(last.key, 0));
   if (!pool || !PyList_Check(pool) || PyList_GET_SIZE(pool) < spares) return nullptr;
-  Owned key(PyTuple_Pack(2, d.o, h.o));
-  PyObject* c = key.o ? PyDict_GetItemWithError(contexts, key.o) : nullptr;
+  PyObject* c = PyDict_GetItemWithError(contexts, last.key);
   Owned value(c ? PyObject_GetAttr(c, s_value) : nullptr);  // of a ctypes.c_void_p
   return value.o && PyLong_Check(value.o) ? static_cast<hf_ctx*>(PyLong_AsVoidPtr(value.o)) : nullptr;
 }
 
-// Runs f (a call of the library) without the interpreter lock.
-template <class F>
-bool called(F&& f) {
-  int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = f();
-  Py_END_ALLOW_THREADS
-  return rc == 0;
-}
+// The interpreter lock given up while this lives.
+struct Unlocked {
+  PyThreadState* state = PyEval_SaveThread();
+  Unlocked() = default;
+  ~Unlocked() { PyEval_RestoreThread(state); }
+  Unlocked(const Unlocked&) = delete;
+  Unlocked& operator=(const Unlocked&) = delete;
+};
 
-// Wraps a function body: None (nothing done) where it gives no result or throws.
+// One call of a function here: what fails before the library is called is left
+// to the Python code, what fails from then on is raised.
+struct Call {
+  bool made = false;
+  // Runs f, a call of the library, without the interpreter lock.
+  template <class F>
+  bool run(hf_ctx* ctx, F&& f) {
+    int rc;
+    {
+      Unlocked u;
+      made = true;
+      rc = f();
+    }
+    if (rc != 0) PyErr_Format(error_type, "histfit error %d: %s", rc, api.last_error(ctx));
+    return rc == 0;
+  }
+};
+
+// Wraps a function body: None (nothing done) where it gives no result or throws
+// before the library's call.
 template <class F>
 PyObject* guarded(Py_ssize_t n, Py_ssize_t want, F&& body) {
   PyObject* r = nullptr;
+  Call call;
   if (n == want && api.nparams) {
     try {
-      if (!modes_active()) r = body();
+      if (!modes_active()) r = body(call);
+    } catch (const std::exception& e) {
+      r = nullptr;
+      if (call.made) PyErr_SetString(PyExc_RuntimeError, e.what());
     } catch (...) {
       r = nullptr;
+      if (call.made) PyErr_SetString(PyExc_RuntimeError, "unknown error");
     }
   }
-  if (r) return r;
+  if (r || call.made) return r;
   PyErr_Clear();
   Py_RETURN_NONE;
 }
@@ -268,7 +304,7 @@ const at::Tensor* theta_of(PyObject* o, int dev, int P) {
 
 // (hist, model, theta, objective, precision, out, status)
 PyObject* fast_eval(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 7, [&]() -> PyObject* {
+  return guarded(n, 7, [&](Call& call) -> PyObject* {
     Hist h(a[0]);
     hf_model m{};
     int P;
@@ -282,7 +318,7 @@ PyObject* fast_eval(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Out out;
     if (!ctx || !th || !status_of(a[6], dev, &st) || !out.take(a[5], *h.c, c10::ScalarType::Double, {1}))
       return nullptr;
-    if (!called([&] {
+    if (!call.run(ctx, [&] {
           return api.eval(ctx, &h.h, &m, static_cast<int32_t>(obj), static_cast<int32_t>(prec),
                           static_cast<const double*>(th->data_ptr()), static_cast<double*>(out.ptr), st,
                           stream);
@@ -295,7 +331,7 @@ PyObject* fast_eval(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (hist, model, theta, objective, precision, seed, want_grad_w, free_mask, nll_out, grad_out,
 //  grad_w_out, status)
 PyObject* fast_grad(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 12, [&]() -> PyObject* {
+  return guarded(n, 12, [&](Call& call) -> PyObject* {
     Hist h(a[0]);
     hf_model m{};
     int P;
@@ -324,7 +360,7 @@ PyObject* fast_grad(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !grad.take(a[9], *h.c, c10::ScalarType::Double, {P}) ||
         (want && !gw.take(a[10], *h.c, c10::ScalarType::Float, h.c->sizes())))
       return nullptr;
-    if (!called([&] {
+    if (!call.run(ctx, [&] {
           return api.grad(ctx, &h.h, &m, static_cast<int32_t>(obj), static_cast<int32_t>(prec),
                           static_cast<const double*>(th->data_ptr()), seed, static_cast<double*>(nll.ptr),
                           static_cast<double*>(grad.ptr), static_cast<float*>(gw.ptr),
@@ -339,7 +375,7 @@ PyObject* fast_grad(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // (hist, model, theta, objective, out, status)
 PyObject* fast_fisher(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 6, [&]() -> PyObject* {
+  return guarded(n, 6, [&](Call& call) -> PyObject* {
     Hist h(a[0]);
     hf_model m{};
     int P;
@@ -355,7 +391,7 @@ PyObject* fast_fisher(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !out.take(a[4], *h.c, c10::ScalarType::Double, {P, P}) ||
         (out.given && THPVariable_Unpack(out.given).numel() != static_cast<int64_t>(P) * P))
       return nullptr;
-    if (!called([&] {
+    if (!call.run(ctx, [&] {
           return api.fisher(ctx, &h.h, &m, static_cast<int32_t>(obj),
                             static_cast<const double*>(th->data_ptr()), static_cast<double*>(out.ptr), st,
                             stream);
@@ -367,7 +403,7 @@ PyObject* fast_fisher(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // (fisher, objective, free_mask, out, status)
 PyObject* fast_covariance(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 5, [&]() -> PyObject* {
+  return guarded(n, 5, [&](Call& call) -> PyObject* {
     const at::Tensor* F = plain(a[0], -1, c10::ScalarType::Double, 1);
     long obj, mask;
     hf_stream_t stream;
@@ -381,7 +417,7 @@ PyObject* fast_covariance(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Out cov, st;
     cov.take(Py_None, *F, c10::ScalarType::Double, F->sizes());
     st.take(Py_None, *F, c10::ScalarType::Int, {B});
-    if (!called([&] {
+    if (!call.run(ctx, [&] {
           return api.covariance(ctx, static_cast<int32_t>(B), static_cast<int32_t>(F->size(-1)),
                                 static_cast<int32_t>(obj), static_cast<const double*>(F->data_ptr()),
                                 static_cast<uint32_t>(mask), static_cast<double*>(cov.ptr),
@@ -395,7 +431,7 @@ PyObject* fast_covariance(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // (events, lo, hi, model, theta, weights, want_grad, nll_out, grad_out, status)
 PyObject* fast_unbinned(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 10, [&]() -> PyObject* {
+  return guarded(n, 10, [&](Call& call) -> PyObject* {
     const at::Tensor* ev = plain(a[0], -1, c10::ScalarType::Double, 1);
     hf_model m{};
     int P;
@@ -419,7 +455,7 @@ PyObject* fast_unbinned(PyObject*, PyObject* const* a, Py_ssize_t n) {
         !nll.take(a[7], *ev, c10::ScalarType::Double, {1}) ||
         !grad.take(a[8], *ev, c10::ScalarType::Double, {P}))
       return nullptr;
-    if (!called([&] {
+    if (!call.run(ctx, [&] {
           return api.unbinned(ctx, static_cast<const double*>(ev->data_ptr()), w, ev->numel(), lo, hi, &m,
                               static_cast<const double*>(th->data_ptr()), static_cast<double*>(nll.ptr),
                               static_cast<double*>(grad.ptr), st, stream);
@@ -433,7 +469,7 @@ PyObject* fast_unbinned(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (counts, offsets, ranges, model, theta0, objective, precision, max_iter, ls_max, fixed_iters,
 //  free_mask, edm_tol, polish_edm, hessian_init, gradient, result type)
 PyObject* fast_fit(PyObject*, PyObject* const* a, Py_ssize_t n) {
-  return guarded(n, 16, [&]() -> PyObject* {
+  return guarded(n, 16, [&](Call& call) -> PyObject* {
     int code, P;
     hf_model m{};
     hf_fit_opts o{};
@@ -467,7 +503,7 @@ PyObject* fast_fit(PyObject*, PyObject* const* a, Py_ssize_t n) {
     st.take(Py_None, *c, c10::ScalarType::Int, {B});
     it.take(Py_None, *c, c10::ScalarType::Int, {B});
     ne.take(Py_None, *c, c10::ScalarType::Int, {B});
-    if (!called([&] {
+    if (!call.run(ctx, [&] {
           return api.fit(ctx, static_cast<int32_t>(B), c->data_ptr(), code,
                          static_cast<const int64_t*>(off->data_ptr()),
                          static_cast<const double*>(rg->data_ptr()), &m, static_cast<int32_t>(obj),
@@ -483,11 +519,12 @@ PyObject* fast_fit(PyObject*, PyObject* const* a, Py_ssize_t n) {
   });
 }
 
-// (handle of libhistfit.so, contexts, pools, spares)
+// (handle of libhistfit.so, contexts, pools, spares, HistfitError)
 PyObject* init_api(PyObject*, PyObject* args) {
-  PyObject *handle, *ctx, *pool;
+  PyObject *handle, *ctx, *pool, *error;
   Py_ssize_t n;
-  if (!PyArg_ParseTuple(args, "OO!O!n", &handle, &PyDict_Type, &ctx, &PyDict_Type, &pool, &n)) return nullptr;
+  if (!PyArg_ParseTuple(args, "OO!O!nO", &handle, &PyDict_Type, &ctx, &PyDict_Type, &pool, &n, &error))
+    return nullptr;
   void* h = PyLong_AsVoidPtr(handle);
   if (!h) return nullptr;
   Api f;
@@ -498,14 +535,18 @@ PyObject* init_api(PyObject*, PyObject* args) {
   f.fisher = reinterpret_cast<decltype(f.fisher)>(dlsym(h, "hf_nll_fisher"));
   f.covariance = reinterpret_cast<decltype(f.covariance)>(dlsym(h, "hf_fisher_covariance"));
   f.fit = reinterpret_cast<decltype(f.fit)>(dlsym(h, "fit_batch"));
-  if (!f.nparams || !f.eval || !f.grad || !f.unbinned || !f.fisher || !f.covariance || !f.fit) {
+  f.last_error = reinterpret_cast<decltype(f.last_error)>(dlsym(h, "hf_last_error"));
+  if (!f.nparams || !f.eval || !f.grad || !f.unbinned || !f.fisher || !f.covariance || !f.fit ||
+      !f.last_error) {
     PyErr_SetString(PyExc_RuntimeError, "libhistfit.so lacks an entry point");
     return nullptr;
   }
   Py_INCREF(ctx);
   Py_INCREF(pool);
+  Py_INCREF(error);
   Py_XSETREF(contexts, ctx);
   Py_XSETREF(pools, pool);
+  Py_XSETREF(error_type, error);
   spares = n;
   api = f;
   Py_RETURN_NONE;
