@@ -127,15 +127,31 @@ void fit_scratch_free(FitScratch* s) {
 int fit_max_cache_bins(int n_gauss, int bkg, int obj, int block) {
   FitLaunchFn fn = pick_fit(n_gauss, bkg, obj, block);
   int m = 0;
-  if (!fn || fn(FitArgs{}, 0, nullptr, &m) != hipSuccess) return 0;
+  if (!fn || fn(FitArgs{}, FIT_ASK_CACHE, nullptr, &m) != hipSuccess) return 0;
   return m > 0 ? m : 0;
 }
 
 int fit_max_wave_bins(int n_gauss, int bkg, int obj, int block) {
   FitLaunchFn fn = pick_fit(n_gauss, bkg, obj, block);
   int m = 0;
-  if (!fn || fn(FitArgs{}, -1, nullptr, &m) != hipSuccess) return 0;
+  if (!fn || fn(FitArgs{}, FIT_ASK_WAVES, nullptr, &m) != hipSuccess) return 0;
   return m > 0 ? m : 0;
+}
+
+// Workgroups of a full launch: no more than are resident at once.  One that
+// starts when others end would still have its first place to do, one of the
+// longest histograms, or in a batch that is not sorted (no more histograms than
+// workgroups) any of them.  (512 histograms of 256..20,000 bins, 512 threads,
+// of which one workgroup fits a CU: 156 us without the limit, 127 with it.)
+static int workgroups(FitLaunchFn fn, const FitArgs& a, int num_cu, FitScratch* s) {
+  const FitScratch::Launch key{reinterpret_cast<const void*>(fn), a.cache_bins, a.wave_bins};
+  auto it = s->resident.find(key);
+  if (it == s->resident.end()) {
+    int n = 0;
+    if (fn(a, FIT_ASK_RESIDENT, nullptr, &n) != hipSuccess || n < 1) n = 1;
+    it = s->resident.emplace(key, n).first;
+  }
+  return num_cu * std::min(s->wg_per_cu, it->second);
 }
 
 // wave_bins of a context set to HF_WAVE_AUTO.  One wave per histogram saves
@@ -156,10 +172,13 @@ static int auto_wave_bins(int n_gauss, int bkg, const FitArgs& a, int grid, cons
 hipError_t launch_fit(int n_gauss, int bkg, FitArgs a, int num_cu, FitScratch* s, hipStream_t st) {
   FitLaunchFn fn = pick_fit(n_gauss, bkg, a.obj, s->block);
   if (!fn) return hipErrorNotSupported;
-  int grid = num_cu * s->wg_per_cu;
-  if (grid > a.B) grid = a.B;
   a.cache_bins = s->cache_bins;
-  a.wave_bins = s->wave_bins != kWaveAuto ? s->wave_bins : auto_wave_bins(n_gauss, bkg, a, grid, s);
+  a.wave_bins = s->wave_bins != kWaveAuto ? s->wave_bins : 0;
+  int grid = std::min(a.B, workgroups(fn, a, num_cu, s));
+  if (s->wave_bins == kWaveAuto) {
+    a.wave_bins = auto_wave_bins(n_gauss, bkg, a, grid, s);
+    grid = std::min(a.B, workgroups(fn, a, num_cu, s));
+  }
   // batches above kMaxRankB run in index order, and so do those of which
   // every workgroup takes one (the order could change nothing)
   a.sorted = (a.B <= kMaxRankB && a.B <= s->cap && (grid < a.B || a.wave_bins > 0)) ? 1 : 0;

@@ -959,8 +959,11 @@ __global__ __launch_bounds__(BLK, 2) void k_fit(FitArgs a) {
     if (tid >= 64)
       for (int j = tid - 64; j < kLogLut; j += BLK - 64) lut[j] = a.log_lut[j];
   }
-  // The first gridDim.x places of the queue belong to the workgroups by index;
-  // the counter hands out the rest.  With no more histograms than workgroups
+  // The first gridDim.x places of the queue, the longest histograms, belong to
+  // the workgroups by index, which spreads them over the CUs (600 histograms of
+  // 256..20,000 bins 107 us; with every place from the counter, two of the
+  // longest end up on one CU: 146); all workgroups are resident, see launch_fit.
+  // The counter hands out the rest.  With no more histograms than workgroups
   // there is no rest, and the queue is not touched (nor re-armed).
   const bool queue = static_cast<int>(gridDim.x) < a.B;
   auto take = [&]() { return queue ? static_cast<int>(gridDim.x + atomicAdd(&a.counters[0], 1u)) : a.B; };
@@ -1009,11 +1012,22 @@ __global__ __launch_bounds__(BLK, 2) void k_fit(FitArgs a) {
   }
 }
 
+// grid > 0 launches; 0, -1 and -2 ask, through *answer, for the largest dynamic
+// LDS cache (u32 bins) that still fits, for the largest wave_bins whose
+// per-wave slots fit, and for the workgroups of a.cache_bins and a.wave_bins
+// that are resident on a CU at once.
+enum : int { FIT_ASK_CACHE = 0, FIT_ASK_WAVES = -1, FIT_ASK_RESIDENT = -2 };
+
 template <int NG, int BKG, int OBJ, int BLK>
-hipError_t launch_fit_kernel(const FitArgs& a, int grid, hipStream_t s, int* max_cache) {
+hipError_t launch_fit_kernel(const FitArgs& a, int grid, hipStream_t s, int* answer) {
+  size_t dyn = sizeof(uint32_t) * static_cast<size_t>(a.cache_bins);
+  if (a.wave_bins > 0) {
+    const size_t w = (BLK / 64) * wave_slot_bytes<NG, BKG>(a.wave_bins);
+    dyn = w > dyn ? w : dyn;
+  }
+  if (grid == FIT_ASK_RESIDENT)
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(answer, k_fit<NG, BKG, OBJ, BLK>, BLK, dyn);
   if (grid <= 0) {
-    // grid 0: the largest dynamic LDS cache (u32 bins) that still fits;
-    // grid -1: the largest wave_bins whose per-wave slots fit
     hipFuncAttributes attr;
     hipError_t e = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(k_fit<NG, BKG, OBJ, BLK>));
     if (e != hipSuccess) return e;
@@ -1023,18 +1037,13 @@ hipError_t launch_fit_kernel(const FitArgs& a, int grid, hipStream_t s, int* max
     e = hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (e != hipSuccess) return e;
     const long free_bytes = static_cast<long>(lds) - static_cast<long>(attr.sharedSizeBytes);
-    if (grid == 0) {
-      *max_cache = static_cast<int>(free_bytes / 4);
+    if (grid == FIT_ASK_CACHE) {
+      *answer = static_cast<int>(free_bytes / 4);
     } else {
       const long per_wave = free_bytes / (BLK / 64) - static_cast<long>(wave_slot_bytes<NG, BKG>(0));
-      *max_cache = per_wave > 0 ? static_cast<int>(per_wave / 16) * 4 : 0;
+      *answer = per_wave > 0 ? static_cast<int>(per_wave / 16) * 4 : 0;
     }
     return hipSuccess;
-  }
-  size_t dyn = sizeof(uint32_t) * static_cast<size_t>(a.cache_bins);
-  if (a.wave_bins > 0) {
-    const size_t w = (BLK / 64) * wave_slot_bytes<NG, BKG>(a.wave_bins);
-    dyn = w > dyn ? w : dyn;
   }
   hipLaunchKernelGGL((k_fit<NG, BKG, OBJ, BLK>), dim3(grid), dim3(BLK), dyn, s, a);
   return hipGetLastError();

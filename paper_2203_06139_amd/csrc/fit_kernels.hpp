@@ -11,6 +11,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
+#include <tuple>
+
 namespace hf {
 
 struct FitArgs {
@@ -50,6 +53,8 @@ constexpr int kWaveAuto = 0x7fffffff;  // HF_WAVE_AUTO: chosen by the batch
 // Device scratch of the fitter, owned by the context.  `order` grows with B;
 // the two counters are cleared once at creation and re-armed by the kernel.
 struct FitScratch {
+  using Launch = std::tuple<const void*, int, int>;  // kernel, cache_bins, wave_bins
+  std::map<Launch, int> resident;  // workgroups per CU that fit at once, by launch
   int32_t* order = nullptr;
   int64_t cap = 0;
   unsigned* counters = nullptr;
