@@ -372,13 +372,13 @@ int hf_fit_get_tuning(const hf_ctx* ctx, int32_t* wg_per_cu, int32_t* cache_bins
  * own, with wave-level reductions and no workgroup barriers; larger
  * histograms keep a whole workgroup each.  0 turns it off.  HF_WAVE_AUTO, the
  * state of a new context, lets the library choose by the batch (up to 2048
- * bins in batches of at least two histograms per workgroup).  It is always
- * off for batches above 65,536 histograms, which run unsorted.  Other values:
- * at most hf_fit_max_wave_bins() for the model, objective and block size,
- * checked by fit_batch (HF_EINVAL).  The results do not depend on it beyond
- * summation order.  Host-only; HF_EINVAL for wave_bins < 0.
- * hf_fit_get_wave_bins returns the setting as set takes it back (or HF_EINVAL
- * for NULL).                                                              */
+ * bins, for batches of at least half as many histograms as the launch has
+ * waves: 1024 at the default shape).  Always off for batches above 65,536
+ * histograms, which run unsorted.  Other values: at most
+ * hf_fit_max_wave_bins() for the model, objective and block size, checked by
+ * fit_batch (HF_EINVAL).  The results do not depend on it beyond summation
+ * order.  Host-only; HF_EINVAL for wave_bins < 0.  hf_fit_get_wave_bins
+ * returns the setting as set takes it back (or HF_EINVAL for NULL).       */
 #define HF_WAVE_AUTO 0x7fffffff
 int hf_fit_set_wave_bins(hf_ctx* ctx, int32_t wave_bins);
 int hf_fit_get_wave_bins(const hf_ctx* ctx);

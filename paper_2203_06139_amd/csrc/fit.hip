@@ -157,28 +157,31 @@ static int workgroups(FitLaunchFn fn, const FitArgs& a, int num_cu, FitScratch* 
 // wave_bins of a context set to HF_WAVE_AUTO.  One wave per histogram saves
 // the workgroup barriers and gives a CU eight fits at once, but each of these
 // fits takes longer, which shows when there are few: so for batches of at
-// least two histograms per workgroup, and up to 2048 bins, where the slots of
-// two workgroups still fit a CU's LDS.  Measured (off, on; us): 16,384 of
+// least half as many histograms as the launch has waves, and up to 2048 bins,
+// less where their slots in LDS would leave fewer workgroups resident.
+// Measured with 512 workgroups of 256 threads (off, on; us): 16,384 of
 // 128..1024 bins 1574, 572; 2048 of 1000 bins 254, 146; 1500 of three
 // Gaussians on 256..2000 bins 477, 292; 1024 of 1000 bins 155, 136; 4096 of
 // 256..65536 bins 1010, 944; 1000 of those 489, 486; but 400 of 10,000 bins
 // (all sorted, none small) 173, 183, and 256 of 1000 bins 70, 96.
-static int auto_wave_bins(int n_gauss, int bkg, const FitArgs& a, int grid, const FitScratch* s) {
-  constexpr int kWaveBins = 2048, kPerGroup = 2;
-  if (a.B > kMaxRankB || a.B / kPerGroup < grid) return 0;
-  return std::min(kWaveBins, fit_max_wave_bins(n_gauss, bkg, a.obj, s->block));
+static int auto_wave_bins(FitLaunchFn fn, int n_gauss, int bkg, FitArgs a, int num_cu, FitScratch* s) {
+  constexpr int kWaveBins = 2048, kStep = 256;
+  const int groups = workgroups(fn, a, num_cu, s);
+  const int waves = std::min(a.B, groups) * (s->block / 64);
+  if (a.B > kMaxRankB || a.B < waves / 2) return 0;
+  for (a.wave_bins = std::min(kWaveBins, fit_max_wave_bins(n_gauss, bkg, a.obj, s->block));
+       a.wave_bins > 0; a.wave_bins -= kStep)
+    if (workgroups(fn, a, num_cu, s) >= groups) return a.wave_bins;
+  return 0;
 }
 
 hipError_t launch_fit(int n_gauss, int bkg, FitArgs a, int num_cu, FitScratch* s, hipStream_t st) {
   FitLaunchFn fn = pick_fit(n_gauss, bkg, a.obj, s->block);
   if (!fn) return hipErrorNotSupported;
   a.cache_bins = s->cache_bins;
-  a.wave_bins = s->wave_bins != kWaveAuto ? s->wave_bins : 0;
-  int grid = std::min(a.B, workgroups(fn, a, num_cu, s));
-  if (s->wave_bins == kWaveAuto) {
-    a.wave_bins = auto_wave_bins(n_gauss, bkg, a, grid, s);
-    grid = std::min(a.B, workgroups(fn, a, num_cu, s));
-  }
+  a.wave_bins = 0;
+  a.wave_bins = s->wave_bins != kWaveAuto ? s->wave_bins : auto_wave_bins(fn, n_gauss, bkg, a, num_cu, s);
+  const int grid = std::min(a.B, workgroups(fn, a, num_cu, s));
   // batches above kMaxRankB run in index order, and so do those of which
   // every workgroup takes one (the order could change nothing)
   a.sorted = (a.B <= kMaxRankB && a.B <= s->cap && (grid < a.B || a.wave_bins > 0)) ? 1 : 0;

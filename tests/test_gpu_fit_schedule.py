@@ -69,3 +69,31 @@ def test_automatic_choice(hf, B):
         hf.fit_set_tuning(*shape)
     assert not np.array_equal(got[0], got[2048])
     np.testing.assert_array_equal(got[hf.WAVE_AUTO], got[2048 if B >= 1024 else 0])
+
+
+@pytest.mark.parametrize("B, on", [(600, False), (1023, False), (1024, True)])
+def test_automatic_choice_counts_waves(hf, B, on):
+    """512 threads, of which one workgroup fits a CU: as many waves as at the
+    default shape, so the same 1024 histograms."""
+    import torch
+    th = [500.0, 0.4, 0.1, 4.0, -0.7]
+    spec = datagen.model_spec(2, 1, -1, 0.0, 1.0)
+    rng = np.random.default_rng(B)
+    lam = datagen.intensity_1d(spec, np.array(th), 700, 0.0, 1.0)
+    c = torch.from_numpy(np.concatenate([datagen.poisson_counts(lam, rng) for _ in range(B)]).view(np.int32)).cuda()
+    off = torch.arange(0, 700 * B + 1, 700).cuda()
+    th0 = torch.as_tensor(np.array([datagen.perturb(th, 0.02, rng) for _ in range(B)])).cuda()
+    rg = torch.tensor([[0.0, 1.0]], dtype=torch.float64).repeat(B, 1).cuda()
+    m = hf.Model.from_spec(spec)
+    was, shape = hf.fit_get_wave_bins(), hf.fit_get_tuning()
+    got = {}
+    try:
+        hf.fit_set_tuning(2, 0, 512)
+        for wb in (hf.WAVE_AUTO, 0, 2048):
+            hf.fit_set_wave_bins(wb)
+            got[wb] = hf.fit_batch(c, off, rg, m, th0).nll.cpu().numpy()
+    finally:
+        hf.fit_set_wave_bins(was)
+        hf.fit_set_tuning(*shape)
+    assert not np.array_equal(got[0], got[2048])
+    np.testing.assert_array_equal(got[hf.WAVE_AUTO], got[2048 if on else 0])
