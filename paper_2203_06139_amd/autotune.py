@@ -128,17 +128,19 @@ def tune_fit(counts, offsets, ranges, model: Model, theta0, objective=POISSON, p
     best = dict(min(ok, key=lambda r: r["ms"]), wave_bins=0)
     fit_set_tuning(best["wg_per_cu"], best["cache_bins"], best["block_size"])
     # second stage, on the chosen shape: one wave per histogram below wave_bins.
-    # The library chooses it for batches of at least two histograms per
-    # workgroup, so a batch of that many is timed with a sample of that many.
+    # The library chooses it for batches of at least half as many histograms as
+    # the launch has waves, so a batch of that many is timed with a sample of that
+    # many.
     capw = fit_max_wave_bins(model, objective, best["block_size"])
     run = lambda: fit_batch(fs.counts, fs.offsets, fs.ranges, model, th0, objective=objective,
                             precision=precision, polish_edm=best["polish_edm"])
     groups = _workgroups(counts, best["wg_per_cu"])
+    need = None if groups is None else groups * best["block_size"] // 128
     sizes = WAVE_BINS
-    if groups is not None and B >= 2 * groups:
+    if need is not None and B >= need:
         sizes = (WAVE_AUTO,) + WAVE_BINS
-        if fs.offsets.numel() - 1 < 2 * groups:
-            fs, th0, ref = draw(2 * groups)
+        if fs.offsets.numel() - 1 < need:
+            fs, th0, ref = draw(need)
             best["ms"] = _time(run)
     for wb in sizes:
         if wb > capw and wb != WAVE_AUTO:
