@@ -31,9 +31,9 @@ __device__ __forceinline__ I run_start(int j, I nb) {
 }
 constexpr int64_t kShort = 1 << 21;  // 2 j nb + 511 stays below 2^31
 
-// Rebinning: one block per histogram, S = 2^slog lanes per coarse bin, S the
-// largest power of two not above the run length nb / 256 (at most 16, a DPP
-// row): lane s takes the run's bins s, s + S, ..., so a wave reads segments of
+// Rebinning: one block per histogram; from six counts per coarse bin on S =
+// 2^slog lanes each, S the largest power of two not above the run length nb / 256
+// (at most 16, a DPP row): lane s takes the run's bins s, s + S, ..., so a wave reads segments of
 // up to 64 bytes, and the S partial sums meet in DPP moves.  U coarse bins are
 // summed side by side over R segments each, which keeps U R loads per lane in
 // flight; positions past a run's end are clamped into the histogram and
@@ -52,6 +52,7 @@ constexpr int64_t kShort = 1 << 21;  // 2 j nb + 511 stays below 2^31
 // loads (101 us for the first), with up to 8 lanes 71.
 template <int slog, int U, int R, class I, class T>
 __device__ __forceinline__ void rebin_runs(const T* __restrict__ c, I nb, double* sum) {
+  static_assert(slog >= 2, "quads at least");
   constexpr int S = 1 << slog;
   const int s = threadIdx.x & (S - 1), group = threadIdx.x >> slog, groups = kMlpIn >> slog;
   const I longest = (nb + kMlpIn - 1) / kMlpIn;  // no run is longer
@@ -82,8 +83,8 @@ __device__ __forceinline__ void rebin_runs(const T* __restrict__ c, I nb, double
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (slog > 0) acc[u] += dpp_row<0xb1>(acc[u]);   // quad_perm [1,0,3,2]
-      if (slog > 1) acc[u] += dpp_row<0x4e>(acc[u]);   // quad_perm [2,3,0,1]
+      acc[u] += dpp_row<0xb1>(acc[u]);                 // quad_perm [1,0,3,2]
+      acc[u] += dpp_row<0x4e>(acc[u]);                 // quad_perm [2,3,0,1]
       if (slog > 2) acc[u] += dpp_row<0x141>(acc[u]);  // row_half_mirror: the other quad of 8
       if (slog > 3) acc[u] += dpp_row<0x140>(acc[u]);  // row_mirror: the other 8 of 16
     }
@@ -94,18 +95,46 @@ __device__ __forceinline__ void rebin_runs(const T* __restrict__ c, I nb, double
   }
 }
 
+// Sum of the n counts from i0 by one thread, R in flight.
+template <int R, class I, class T>
+__device__ __forceinline__ double own_run(const T* __restrict__ c, I nb, I i0, I n) {
+  const I longest = (nb + kMlpIn - 1) / kMlpIn;
+  double s = 0.0;
+  for (I k0 = 0; k0 < longest; k0 += R) {
+    T v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = c[i0 + k0 + r < nb ? i0 + k0 + r : nb - 1];
+#pragma unroll
+    for (int r = 0; r < R; ++r) s += static_cast<double>(k0 + r < n ? v[r] : static_cast<T>(0));
+  }
+  return s;
+}
+
+// Mean of coarse bin threadIdx.x's counts, 0 where it has none.  Runs of up to
+// six counts are left to the bin's own thread, without LDS and a barrier: 4096
+// histograms of 100, 700, 1020, 1500 and 2040 bins 9.0, 9.7, 10.4, 11.6, 19.7 us,
+// with lanes per run 10.3, 12.0, 12.3, 14.0, 14.3 (a thread walking the run one
+// count after the other: 9.3, 10.4, 12.0, 13.1, 22.6).
 template <class I, class T>
-__device__ __forceinline__ void rebin_all(const T* __restrict__ c, I nb, double* sum) {
-  if (nb >= 4096)
-    rebin_runs<4, 4, 4, I>(c, nb, sum);
-  else if (nb >= 2048)
-    rebin_runs<3, 8, 1, I>(c, nb, sum);
-  else if (nb >= 1024)
-    rebin_runs<2, 4, 1, I>(c, nb, sum);
-  else if (nb >= 512)
-    rebin_runs<1, 2, 1, I>(c, nb, sum);
-  else
-    rebin_runs<0, 1, 1, I>(c, nb, sum);
+__device__ __forceinline__ double coarse_mean(const T* __restrict__ c, I nb, double* sum) {
+  const int j = threadIdx.x;
+  const I i0 = run_start<I>(j, nb), n = run_start<I>(j + 1, nb) - i0;
+  double s;
+  if (nb < 512) {
+    s = own_run<2, I>(c, nb, i0, n);
+  } else if (nb < 1536) {
+    s = own_run<4, I>(c, nb, i0, n);
+  } else {
+    if (nb >= 4096)
+      rebin_runs<4, 4, 4, I>(c, nb, sum);
+    else if (nb >= 2048)
+      rebin_runs<3, 8, 1, I>(c, nb, sum);
+    else
+      rebin_runs<2, 4, 1, I>(c, nb, sum);
+    __syncthreads();
+    s = sum[j];
+  }
+  return n > 0 ? s / static_cast<double>(n) : 0.0;
 }
 
 template <class T>
@@ -117,17 +146,13 @@ __global__ __launch_bounds__(kMlpIn) void k_rebin_lognorm(const T* __restrict__ 
   const int b = blockIdx.x;
   const int64_t off = offsets[b];
   const int64_t nb = offsets[b + 1] - off;
-  const int j = threadIdx.x;  // coarse bin
-  if (nb < 1)
-    sum[j] = 0.0;  // empty histogram (uniform over the block)
-  else if (nb < kShort)
-    rebin_all<int>(counts + off, static_cast<int>(nb), sum);
-  else
-    rebin_runs<4, 4, 4, int64_t>(counts + off, nb, sum);
-  __syncthreads();
-  const double k = static_cast<double>(run_start<int64_t>(j + 1, nb) - run_start<int64_t>(j, nb));
-  const double v = k > 0.0 ? log1p(sum[j] / k) : 0.0;
-  out[static_cast<int64_t>(b) * kMlpIn + j] = static_cast<float>((v - in_mean) / in_std);
+  double mean = 0.0;  // of an empty histogram (uniform over the block)
+  if (nb >= kShort)
+    mean = coarse_mean<int64_t>(counts + off, nb, sum);
+  else if (nb >= 1)
+    mean = coarse_mean<int>(counts + off, static_cast<int>(nb), sum);
+  out[static_cast<int64_t>(b) * kMlpIn + threadIdx.x] =
+      static_cast<float>((log1p(mean) - in_mean) / in_std);
 }
 
 hipError_t rebin_lognorm(int B, const void* counts, int dtype, const int64_t* offsets, float mean,
