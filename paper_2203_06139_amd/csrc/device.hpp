@@ -57,10 +57,10 @@ struct Model1D {
   // `recur` is set when every Gaussian satisfies K |dz| <= 1 and the
   // exponential background K |b1 dt| <= 1 (see chunk_1d).
   double dz[NG > 0 ? NG : 1], D[NG > 0 ? NG : 1];
-  double Dm[NG > 0 ? NG : 1];  // 1 - D to full relative accuracy, for run_1d
+  double Dm[NG > 0 ? NG : 1];  // 1 - D to full relative accuracy (init_wave, for run_1d)
   double dt;
   double qE;   // exponential background: ratio exp(b1 dt) of neighbouring bins
-  double qEm;  // qE - 1 to full relative accuracy, for run_1d
+  double qEm;  // qE - 1 to full relative accuracy (init_wave, for run_1d)
   bool recur;
 
   __device__ __forceinline__ void init(const double* __restrict__ th, double t_shift,
@@ -82,16 +82,13 @@ struct Model1D {
     for (int g = 0; g < NG; ++g) {
       dz[g] = h * is[g];
       D[g] = exp_fast(-dz[g] * dz[g]);
-      Dm[g] = -expm1_fast(-dz[g] * dz[g]);
     }
     dt = h * ta;
     qE = 1.0;
-    qEm = 0.0;
     if constexpr (BKG == BKG_EXP) {
       // E_{k+1} = E_k exp(b1 dt): exact ratio on the grid; K |b1 dt| <= 1
       // keeps q^K within [1/e, e], so the product loses no range
       qE = exp_fast(c[1] * dt);
-      qEm = expm1_fast(c[1] * dt);
     }
     recur = recurs(K);
   }

@@ -177,7 +177,7 @@ struct RunCounts {
 // wave (BLK = 64) for the small histograms at the end of the longest-first
 // queue.  gtid is the thread's index in its group, gsync the group's
 // barrier (for a wave: LDS operations stay in program order, so a fence and
-// a code-motion barrier are enough), group_sum the group's fixed-order sum.
+// a code-motion barrier are enough).
 template <int BLK>
 __device__ __forceinline__ int gtid() {
   return BLK == 64 ? static_cast<int>(threadIdx.x & 63u) : static_cast<int>(threadIdx.x);

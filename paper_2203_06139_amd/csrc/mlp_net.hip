@@ -143,6 +143,9 @@ __device__ __forceinline__ void tile_product(const uint16_t* act, const uint16_t
 
 // Stores ROWS staged rows of N values: row-major at `rm` and, in training,
 // in fragment order over the batch (tiles of 16 columns, K = rows) at `fo`.
+// The row-major copies are the workspace's documented contents; no kernel
+// reads them (14.7 MB for 4096 rows of inference, 3 us at a copy's rate, next to
+// the products).
 template <int ROWS, int N, bool TRAIN>
 __device__ __forceinline__ void store_rows(const uint16_t* act, int64_t row0, int B, uint16_t* rm,
                                            uint16_t* fo) {

@@ -134,7 +134,6 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
     // path: za = z at the chunk's first centre, ea = phi at the current
     // centre and Ea its ratio to the next one
     double za[G1], Ea[G1], ea[G1];
-    double xa = fma(static_cast<double>(i0), a.hx, a.x0);
     if (series) {
       const double xc = fma(static_cast<double>(i0) + 0.5, a.hx, a.x0);
 #pragma unroll
@@ -144,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
         Ea[g] = exp_fast(fmin(fmax(fma(-dzs[g], za[g], -0.5 * dzs[g] * dzs[g]), -700.0), 700.0));
       }
     } else {
-      const double x = xa;
+      const double x = fma(static_cast<double>(i0), a.hx, a.x0);
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         za[g] = (x - M.m[g]) * M.is[g];
@@ -248,7 +247,6 @@ __global__ __launch_bounds__(kBlock) void k_nll_1d_avg(NllArgs a) {
         for (int p = 0; p < P; ++p) acc[1 + p] = fma(mb, J[p], acc[1 + p]);
       }
       if (a.grad_w_out) a.grad_w_out[i] = static_cast<float>(seed * l);
-      xa = xb;
     }
   }
   // exact partials: no final factors
